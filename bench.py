@@ -64,14 +64,14 @@ def sigma_kernel_name(prec, nv):
     t16 = -(-nv // 16)
     t32 = 2 * -(-nv // 32)
     if prec == "fp64":
-        k = "k_sandwich_f64 (software-pipelined)" if t16 >= 20 else "k_sandwich<double> (two workgroups per CU)"
+        k = "k_sigma_mm<double> (two products in one kernel; k_sandwich<double> for blocks of under 16 column tiles)"
     elif prec == "fp32":
-        k = "k_sandwich<float>"
+        k = "k_sigma_mm<float> (two products in one kernel; k_sandwich<float> for blocks of under 18 column tiles)"
     elif prec == "bf16x6" and t32 >= 32 and t32 % 8 == 0:
         k = "k_sandwich_bf16w (double-buffered, 8-column panels)"
     else:
         k = "k_sandwich_bf16<%d>" % (6 if prec == "bf16x6" else 3)
-    return k + ": fused density-fitted sigma contraction"
+    return k + ": density-fitted sigma contraction"
 
 
 def log(*a):

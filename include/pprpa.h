@@ -318,7 +318,7 @@ typedef struct {
   int32_t status;       /* pprpa_status of the solve (meaningful once done)                  */
   int32_t nroot;
   int32_t max_overtaken; /* the most times the grouped sigma launches of another kernel
-                            variant (the sigma precision, and for FP64 the kernel chosen by the
+                            variant (the sigma precision, and for BF16X6 the kernel chosen by the
                             size of the virtual block) went ahead of one of this request's
                             waiting sigma blocks; the variant of the longest-waiting block goes
                             first, so this is at most 4 (one per other variant)               */

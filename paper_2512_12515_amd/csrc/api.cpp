@@ -8,6 +8,7 @@
 #include <mutex>
 #include <numeric>
 
+#include "sigma_mm.h"
 #include "solver.h"
 
 namespace pprpa {
@@ -76,21 +77,17 @@ pprpa_status dalloc(pprpa_ctx* c, size_t bytes, void** p) {
   return PPRPA_OK;
 }
 
-// Aux-index splits of a sigma launch: about 8192 workgroups (32 per CU), which measured best on
-// MI355X (shorter tails and better balance than 1.5k-4k; partial sums stay small).
-int nsplit_of(int variant, int nitems, int naux, int k) {
-  // work units per launch: the FP64 kernel runs one 8-wave workgroup per CU, the others two
-  // 4-wave workgroups
-  const int target = variant == 5 ? UNITS_F64 : 8192;
-  const int per = std::max(1, nitems * k);
-  int ns = (target + per - 1) / per;
+// Aux-index splits of a sigma launch of the one-kernel form: about 8192 workgroups (32 per CU),
+// which measured best on MI355X (shorter tails and better balance than 1.5k-4k; partial sums stay
+// small).
+int nsplit_of(const SigmaPlan& plan, int naux, int k) {
+  const int per = std::max(1, plan.unit_items * k);
+  int ns = (plan.units + per - 1) / per;
   ns = std::min(ns, std::min(naux, 256));
   return std::max(1, ns);
 }
 
-int nsplit_for(const pprpa_ctx* c, int k) {
-  return nsplit_of(c->plan.variant, c->plan.nitems, c->g.naux, k);
-}
+int nsplit_for(const pprpa_ctx* c, int k) { return nsplit_of(c->plan, c->g.naux, k); }
 
 static pprpa_status get_event(pprpa_ctx* c, hipEvent_t* e) {
   if (!c->pool.empty()) {
@@ -171,9 +168,10 @@ pprpa_status sigma_device(pprpa_ctx* c, int k, const double* dz, double* ds) {
                  2.0 * kk * (double)n * 8.0;
       PPRPA_TRY(gated_launch(c, tm, [&] {
         return launch_sigma_ab(ag, c->st, c->nprod, c->plan, c->L, c->Lb, c->ZT, c->zplane, c->Sp, kk,
-                               ns, c->stream);
+                               ns, c->sp_slots, c->stream);
       }));
-      PPRPA_HIP(launch_epilogue_ab(ag, c->st, z, kk, c->Sp, ns, c->epair, s, c->stream));
+      const SigmaSums q = sigma_sums(ag, c->st, kk, ns);
+      PPRPA_HIP(launch_epilogue_ab(ag, q, z, kk, c->Sp, c->epair, s, c->stream));
     }
     return PPRPA_OK;
   }
@@ -193,6 +191,7 @@ pprpa_status sigma_device(pprpa_ctx* c, int k, const double* dz, double* ds) {
     la.Sp = c->Sp;
     la.k = kk;
     la.nsplit = ns;
+    la.ws_slots = c->sp_slots;
     la.npan_v = c->plan.npan_v;
     la.npan_o = 0;
     la.plane = c->plane;
@@ -208,7 +207,8 @@ pprpa_status sigma_device(pprpa_ctx* c, int k, const double* dz, double* ds) {
     tm.bytes = (double)g.naux * ((double)g.nv * g.nv + (double)g.nv * g.no + (double)g.no * g.no) * esz +
                2.0 * kk * (double)n * 8.0;
     PPRPA_TRY(gated_launch(c, tm, [&] { return launch_sigma(c->g, c->st, c->plan, la, c->stream); }));
-    PPRPA_HIP(launch_epilogue(c->g, c->st, z, kk, c->Sp, ns, c->ptab, c->epair, s, c->stream));
+    const SigmaSums q = sigma_sums(c->g, c->st, kk, ns);
+    PPRPA_HIP(launch_epilogue(c->g, q, z, kk, c->Sp, c->epair, s, c->stream));
   }
   return PPRPA_OK;
 }
@@ -306,6 +306,21 @@ pprpa_status setup_runtime(pprpa_ctx* c, void* stream) {
     PPRPA_HIP(hipHostMalloc((void**)&c->pinned, c->pinned_elems * sizeof(double), hipHostMallocDefault));
   PPRPA_HIP(prepare_kernels());
   return PPRPA_OK;
+}
+
+// Partial sums of a sigma launch: at least `slots` matrices of `bytes` each. A context that runs the
+// two-product form outside a slab takes up to MM_WORKSPACE bytes instead, so that its products need
+// fewer, longer launches; it does with the least when that much is not free.
+pprpa_status alloc_sums(pprpa_ctx* c, const MmGeometry& mg, size_t slots, size_t bytes) {
+  c->sp_slots = (int64_t)slots;
+  if (!c->slab && mm_plan(c->st, mg, c->kcap, nsplit_for(c, c->kcap) * c->kcap).nslot > 0) {
+    const size_t more = std::min(slots + (size_t)mg.naux * c->kcap, MM_WORKSPACE / bytes);
+    if (more > slots && dalloc(c, more * bytes, &c->Sp) == PPRPA_OK) {
+      c->sp_slots = (int64_t)more;
+      return PPRPA_OK;
+    }
+  }
+  return dalloc(c, slots * bytes, &c->Sp);
 }
 
 pprpa_status build_impl(const pprpa_build_args* a, pprpa_ctx* c) {
@@ -435,12 +450,8 @@ pprpa_status build_impl(const pprpa_build_args* a, pprpa_ctx* c) {
   if (bad) return einval("Lpq contains non-finite values");
 
   // ---- sigma plan and workspaces ---------------------------------------------------------
-  int RT = 16;
-  c->plan.variant = sigma_variant(g, c->st, c->nprod, &RT);
-  c->plan.RT = RT;
   std::vector<int> items;
-  make_sigma_items(g, RT, items, c->plan.npan_v, panel_width(c->plan.variant));
-  c->plan.nitems = (int)items.size();
+  make_sigma_plan(g, c->st, c->nprod, c->plan, items);
   PPRPA_TRY(dalloc(c, items.size() * sizeof(int), (void**)&c->plan.d_items));
   PPRPA_HIP(hipMemcpyAsync(c->plan.d_items, items.data(), items.size() * sizeof(int),
                            hipMemcpyHostToDevice, c->stream));
@@ -452,7 +463,7 @@ pprpa_status build_impl(const pprpa_build_args* a, pprpa_ctx* c) {
   PPRPA_TRY(dalloc(c, c->zplane * esz * nplanes, &c->ZT));
   PPRPA_HIP(hipMemsetAsync(c->ZT, 0, c->zplane * esz * nplanes, c->stream));
   const size_t spsz = c->st == Store::F64 ? 8 : 4;
-  PPRPA_TRY(dalloc(c, sp_max * zz * spsz, &c->Sp));
+  PPRPA_TRY(alloc_sums(c, mm_geometry(g), sp_max, zz * spsz));
   PPRPA_TRY(dalloc(c, (size_t)c->kcap * g.n * sizeof(double), (void**)&c->zbuf));
   PPRPA_TRY(dalloc(c, (size_t)c->kcap * g.n * sizeof(double), (void**)&c->sbuf));
 
@@ -614,14 +625,15 @@ pprpa_status build_ab_impl(const pprpa_build_ab_args* a, pprpa_ctx* c) {
     PPRPA_HIP(hipMemsetAsync(c->ZT, 0, zt * esz * nplanes, c->stream));
     std::vector<int> items;
     make_sigma_items_ab(ag, items, c->plan.npan_v);
-    c->plan.nitems = (int)items.size();
+    c->plan.nitems = c->plan.unit_items = (int)items.size();
     PPRPA_TRY(dalloc(c, items.size() * sizeof(int), (void**)&c->plan.d_items));
     PPRPA_HIP(hipMemcpyAsync(c->plan.d_items, items.data(), items.size() * sizeof(int),
                              hipMemcpyHostToDevice, c->stream));
     size_t sp_max = 0;
     for (int kk = 1; kk <= c->kcap; ++kk)
       sp_max = std::max(sp_max, (size_t)nsplit_for(c, kk) * kk);
-    PPRPA_TRY(dalloc(c, sp_max * ag.nmopa * ag.nmopb * (c->st == Store::F64 ? 8 : 4), &c->Sp));
+    PPRPA_TRY(alloc_sums(c, mm_geometry(ag), sp_max,
+                         (size_t)ag.nmopa * ag.nmopb * (c->st == Store::F64 ? 8 : 4)));
   } else {
     PPRPA_TRY(dalloc(c, (size_t)g.n * g.n * sizeof(double), (void**)&c->M));
     PPRPA_HIP(launch_dense_build_ab(La, Lb, naux, nmo, noa, nob, g.n, g.nvv, c->ptab, c->epair,
@@ -677,15 +689,14 @@ size_t context_footprint(const pprpa_build_args* a, const pprpa_davidson_args* d
     b += al((size_t)staging_chunk(per, g.naux) * per * sizeof(double));
   }
   if (a->dense && st != Store::F64) b += al(plane * sizeof(double));
-  int RT = 16, npan_v = 0;
-  const int variant = sigma_variant(g, st, a->prec == PPRPA_BF16X3 ? 3 : 6, &RT);
+  SigmaPlan plan;
   std::vector<int> items;
-  make_sigma_items(g, RT, items, npan_v, panel_width(variant));
+  make_sigma_plan(g, st, a->prec == PPRPA_BF16X3 ? 3 : 6, plan, items);
   b += al(items.size() * sizeof(int));
   b += al((size_t)kcap * zz * esz * nplanes);       // unpacked vectors
   size_t sp_max = 0;
   for (int kk = 1; kk <= kcap; ++kk)
-    sp_max = std::max(sp_max, (size_t)nsplit_of(variant, (int)items.size(), g.naux, kk) * kk);
+    sp_max = std::max(sp_max, (size_t)nsplit_of(plan, g.naux, kk) * kk);
   b += al(sp_max * zz * (st == Store::F64 ? 8 : 4));  // partial sums
   b += 2 * al((size_t)kcap * g.n * sizeof(double));   // host-vector staging
   if (a->dense) b += al((size_t)g.n * g.n * sizeof(double));

@@ -24,7 +24,8 @@ struct pprpa_ctx {
   double* epair = nullptr;  // +(e_a+e_b) / -(e_i+e_j) per packed pair
   void* ZT = nullptr;       // unpacked vectors [kcap][nmop][nmop] (3 planes for BF16)
   size_t zplane = 0;
-  void* Sp = nullptr;       // sigma partial sums
+  void* Sp = nullptr;       // sigma partial sums (and workspace of the two-product form)
+  int64_t sp_slots = 0;     // its size in nmop x nmop matrices of the sigma precision
   double* zbuf = nullptr;   // [kcap][n] staging of host vectors
   double* sbuf = nullptr;
   double* M = nullptr;      // dense matrix [n][n] (dense builds)
@@ -66,7 +67,7 @@ namespace pprpa {
 // sigma = M z for k vectors already on the device ([k][n] each), on the context's stream.
 pprpa_status sigma_device(pprpa_ctx* c, int k, const double* dz, double* ds);
 int nsplit_for(const pprpa_ctx* c, int k);
-int nsplit_of(int variant, int nitems, int naux, int k);
+int nsplit_of(const SigmaPlan& plan, int naux, int k);
 
 pprpa_status dalloc(pprpa_ctx* c, size_t bytes, void** p);
 // Fold completed launch timings into c->stats (call after synchronising the stream).

@@ -59,6 +59,8 @@ struct Geometry {
   int64_t nvv = 0, noo = 0, n = 0;
 };
 
+struct AbGeometry;
+
 // A served context's device memory: one contiguous reservation, handed out by bumping `top`
 // (nothing is freed until the whole reservation is released).
 struct Slab {
@@ -76,6 +78,7 @@ struct SigmaLaunch {
   void* Sp;          // partial sums [nsplit][k][nmop][nmop]
   int k;             // vectors in the block
   int nsplit;        // aux-index splits
+  int64_t ws_slots;  // size of Sp in nmop x nmop matrices
   int npan_v, npan_o;
   size_t plane;      // elements per bf16 plane of L (BF16 only)
   size_t zplane;     // elements per bf16 plane of ZT (BF16 only)
@@ -87,16 +90,25 @@ struct SigmaPlan {
   int variant = 0;
   int RT = 16;
   int nitems = 0;
+  int units = 8192, unit_items = 0;  // a product's aux splits: units / (unit_items k)
   int npan_v = 0;
   int* d_items = nullptr;
 };
-// Work items (panel index << 16 | first row tile): panels of pw adjacent column tiles of one
-// diagonal block, row ranges of RT tiles.
-void make_sigma_items(const Geometry& g, int RT, std::vector<int>& items, int& npan_v, int pw = 4);
-// Column tiles per panel of a sigma kernel variant.
-inline int panel_width(int variant) { return variant == 7 ? 8 : 4; }
-constexpr int UNITS_F64 = 16384;      // work units per launch of the pipelined FP64 kernel
-constexpr int F64_PIPE_MIN_NVT = 20;  // virtual 16-tiles from which FP64 sigma uses that kernel
+// The partial sums of a product of k vectors that its epilogue adds up: their type; the virtual
+// block's number, vector stride and split stride (rows of the padded layout); the occupied block's
+// number, start, row length and strides. All in elements.
+struct SigmaSums {
+  Store st;
+  int nsplit;
+  int64_t vec, split;
+  int nsplit_o;
+  int64_t off_o, ld_o, vec_o, split_o;
+};
+SigmaSums sigma_sums(const Geometry& g, Store st, int k, int nsplit);
+SigmaSums sigma_sums(const AbGeometry& g, Store st, int k, int nsplit);
+// Kernel variant of a restricted context and its work items (panel index << 16 | first row tile):
+// panels of adjacent column tiles of one diagonal block, row ranges of RT tiles.
+void make_sigma_plan(const Geometry& g, Store st, int nprod, SigmaPlan& plan, std::vector<int>& items);
 constexpr int BF16_WIDE_MIN_NVT = 32;  // the same for the wide-panel BF16x6 kernel
 // Largest order of the dense pencil solves on the device (the direct diagonalisation and the
 // whole-spectrum solve of the correlation energy), and the largest order solved by one
@@ -104,7 +116,6 @@ constexpr int BF16_WIDE_MIN_NVT = 32;  // the same for the wide-panel BF16x6 ker
 constexpr int DENSE_SOLVE_MAX = 8192;
 constexpr int DENSE_ENERGY_MAX = 8192;
 constexpr int DENSE_ONE_WG_MAX = 96;
-int sigma_variant(const Geometry& g, Store st, int nprod, int* RT);
 
 // --- kernel launchers (k_sigma.hip) -------------------------------------------------------
 hipError_t launch_stage_L(const Geometry& g, Store st, const double* Lin, int nin, int p0, int np,
@@ -118,13 +129,13 @@ hipError_t launch_sigma(const Geometry& g, Store st, const SigmaPlan& plan, cons
 constexpr int GROUP_MAX = 16;
 struct GroupMember {
   const Geometry* g;
+  Store st;
   const SigmaPlan* plan;
   SigmaLaunch la;
 };
 hipError_t launch_sigma_group(const GroupMember* m, int n, hipStream_t s);
-hipError_t launch_epilogue(const Geometry& g, Store st, const double* z, int k, const void* Sp,
-                           int nsplit, const int* d_ptab, const double* d_epair, double* sigma,
-                           hipStream_t s);
+hipError_t launch_epilogue(const Geometry& g, const SigmaSums& q, const double* z, int k,
+                           const void* Sp, const double* d_epair, double* sigma, hipStream_t s);
 hipError_t launch_check_finite(const double* x, size_t n, int* d_bad, hipStream_t s);
 
 // Alpha-beta sector of unrestricted ppRPA, density fitted: each spin's orbitals in the padded
@@ -151,11 +162,10 @@ hipError_t launch_unpack_ab(const AbGeometry& g, Store st, const double* z, int 
 // for BF16, whose nprod = 6 or 3 products; La, Lb then three planes of naux nmop^2 each).
 hipError_t launch_sigma_ab(const AbGeometry& g, Store st, int nprod, const SigmaPlan& plan,
                            const void* La, const void* Lb, const void* ZT, size_t zplane, void* Qp,
-                           int k, int nsplit, hipStream_t s);
+                           int k, int nsplit, int64_t ws_slots, hipStream_t s);
 // sigma [k][n] = epair * z + the split sums of Qp (fixed order, FP64).
-hipError_t launch_epilogue_ab(const AbGeometry& g, Store st, const double* z, int k,
-                              const void* Qp, int nsplit, const double* epair, double* sigma,
-                              hipStream_t s);
+hipError_t launch_epilogue_ab(const AbGeometry& g, const SigmaSums& q, const double* z, int k,
+                              const void* Qp, const double* epair, double* sigma, hipStream_t s);
 
 // --- dense (k_dense.hip) -------------------------------------------------------------------
 hipError_t launch_dense_build(const Geometry& g, const double* L64, const int* d_ptab,

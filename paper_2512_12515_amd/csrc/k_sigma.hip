@@ -38,6 +38,7 @@
 #include "internal.h"
 #include "sigma_common.h"
 #include "sigma_bf16.h"
+#include "sigma_mm.h"
 
 namespace pprpa {
 namespace {
@@ -454,10 +455,9 @@ constexpr int ET = 16;
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_epilogue(const double* __restrict__ z, int64_t n,
-                                                  int64_t nvv, int nv, int no, int nvp, int nmop,
-                                                  int mult, const T* __restrict__ Sp, int nsplit,
-                                                  int64_t split_stride, int ntv, int npv,
-                                                  const double* __restrict__ epair,
+                                                  int64_t nvv, int nv, int no, int nmop, int mult,
+                                                  const T* __restrict__ Sp, SigmaSums q,
+                                                  int npv, const double* __restrict__ epair,
                                                   double* __restrict__ sigma) {
   __shared__ double mirror[ET][ET + 1];
   const int kv = blockIdx.y;
@@ -466,7 +466,6 @@ __global__ __launch_bounds__(256) void k_epilogue(const double* __restrict__ z, 
   if (!vblk) tp -= npv;
   const int nb = vblk ? nv : no;
   const int nt = (nb + ET - 1) / ET;
-  const int off = vblk ? 0 : nvp;
   int I = 0;  // tile pair tp -> (I, J), row-major over the upper triangle of tiles
   while (tp >= nt - I) {
     tp -= nt - I;
@@ -477,9 +476,11 @@ __global__ __launch_bounds__(256) void k_epilogue(const double* __restrict__ z, 
   const int pa = I * ET + r, qa = J * ET + c;  // element of the tile
   const int pb = J * ET + r, qb = I * ET + c;  // element of the mirror tile
   const bool oka = pa < nb && qa < nb, okb = pb < nb && qb < nb;
-  const T* Q = Sp + (int64_t)kv * nmop * nmop;
-  const int64_t ia = (int64_t)(off + pa) * nmop + off + qa;
-  const int64_t ib = (int64_t)(off + pb) * nmop + off + qb;
+  const T* Q = Sp + (vblk ? kv * q.vec : q.off_o + kv * q.vec_o);
+  const int64_t ld = vblk ? nmop : q.ld_o;
+  const int64_t ia = pa * ld + qa, ib = pb * ld + qb;
+  const int nsplit = vblk ? q.nsplit : q.nsplit_o;
+  const int64_t split_stride = vblk ? q.split : q.split_o;
   // both elements lie in the padded block, which every split writes in full: the loads are
   // unconditional (so that the unrolled iterations issue them together), the padding is
   // discarded afterwards
@@ -497,9 +498,9 @@ __global__ __launch_bounds__(256) void k_epilogue(const double* __restrict__ z, 
   if (!oka || qa < pa + k) return;
   // Q[q][p] for (p, q) = (pa, qa) is the mirror tile's element (qa - J ET, pa - I ET) = (c, r)
   const double s = mult == 0 ? a + mirror[c][r] : a - mirror[c][r];
-  const int64_t p = pa, q = qa;
-  const int64_t e = (vblk ? 0 : nvv) + p * (nb - k) - p * (p - 1) / 2 + (q - p - k);
-  const double nrm = (mult == 0 && p == q) ? 0.70710678118654752440 : 1.0;
+  const int64_t p = pa;
+  const int64_t e = (vblk ? 0 : nvv) + p * (nb - k) - p * (p - 1) / 2 + (qa - p - k);
+  const double nrm = (mult == 0 && pa == qa) ? 0.70710678118654752440 : 1.0;
   sigma[(int64_t)kv * n + e] = epair[e] * z[(int64_t)kv * n + e] + nrm * s;
 }
 
@@ -550,27 +551,22 @@ hipError_t launch_unpack(const Geometry& g, Store st, const double* z, int k, co
   return hipGetLastError();
 }
 
-hipError_t launch_epilogue(const Geometry& g, Store st, const double* z, int k, const void* Sp,
-                           int nsplit, const int* d_ptab, const double* d_epair, double* sigma,
-                           hipStream_t s) {
-  (void)d_ptab;
+hipError_t launch_epilogue(const Geometry& g, const SigmaSums& q, const double* z, int k,
+                           const void* Sp, const double* d_epair, double* sigma, hipStream_t s) {
   const int ntv = (g.nv + ET - 1) / ET, nto = (g.no + ET - 1) / ET;
   const int npv = ntv * (ntv + 1) / 2, npo = nto * (nto + 1) / 2;
   dim3 grid((unsigned)(npv + npo), (unsigned)k);
-  const int64_t split_stride = (int64_t)k * g.nmop * g.nmop;
-  if (st == Store::F64)
-    hipLaunchKernelGGL(k_epilogue<double>, grid, dim3(256), 0, s, z, g.n, g.nvv, g.nv, g.no, g.nvp,
-                       g.nmop, g.mult, (const double*)Sp, nsplit, split_stride, ntv, npv, d_epair,
-                       sigma);
+  if (q.st == Store::F64)
+    hipLaunchKernelGGL(k_epilogue<double>, grid, dim3(256), 0, s, z, g.n, g.nvv, g.nv, g.no, g.nmop,
+                       g.mult, (const double*)Sp, q, npv, d_epair, sigma);
   else
-    hipLaunchKernelGGL(k_epilogue<float>, grid, dim3(256), 0, s, z, g.n, g.nvv, g.nv, g.no, g.nvp,
-                       g.nmop, g.mult, (const float*)Sp, nsplit, split_stride, ntv, npv, d_epair,
-                       sigma);
+    hipLaunchKernelGGL(k_epilogue<float>, grid, dim3(256), 0, s, z, g.n, g.nvv, g.nv, g.no, g.nmop,
+                       g.mult, (const float*)Sp, q, npv, d_epair, sigma);
   return hipGetLastError();
 }
 
-// Work items: (panel, first row tile) pairs; a panel spans up to 4 column tiles of one block.
-void make_sigma_items(const Geometry& g, int RT, std::vector<int>& items, int& npan_v, int pw) {
+// Work items: (panel, first row tile) pairs; a panel spans up to pw column tiles of one block.
+static void sigma_items(const Geometry& g, int RT, int pw, std::vector<int>& items, int& npan_v) {
   items.clear();
   const int not_ = g.nct - g.nvt;
   npan_v = (g.nvt + pw - 1) / pw;
@@ -581,23 +577,20 @@ void make_sigma_items(const Geometry& g, int RT, std::vector<int>& items, int& n
   }
 }
 
-int sigma_variant(const Geometry& g, Store st, int nprod, int* RT) {
-  if (st == Store::F64) {
-    // the software-pipelined kernel (k_sigma_f64.hip) for large virtual blocks; below that its
-    // units are too short to keep the pipeline full and the two-workgroup kernel is faster
-    if (g.nvt >= F64_PIPE_MIN_NVT) {
-      *RT = 32;
-      return 5;
-    }
-    *RT = 16;
-    return 1;
-  }
-  if (st == Store::F32) { *RT = 32; return 4; }
-  *RT = 32;
+void make_sigma_plan(const Geometry& g, Store st, int nprod, SigmaPlan& plan, std::vector<int>& items) {
   // BF16 split, six products: the double-buffered wide-panel kernel (k_sigma_bf16.hip) for
   // large virtual blocks that it tiles with full 8-tile panels (a ragged last panel idles waves
   // of its workgroup: at 26 tiles = 3 x 8 + 2 it measured no faster than the 4-tile kernel)
-  return nprod == 6 && g.nvt >= BF16_WIDE_MIN_NVT && g.nvt % 8 == 0 ? 7 : 3;
+  const bool wide = st == Store::BF16 && nprod == 6 && g.nvt >= BF16_WIDE_MIN_NVT && g.nvt % 8 == 0;
+  plan.variant = st == Store::F64 ? 1 : (st == Store::F32 ? 4 : (wide ? 7 : 3));
+  // large FP64 blocks: the workspace of 16384 units of 32 row tiles, for the two-product form
+  const bool large = st == Store::F64 && g.nvt >= 20;
+  plan.units = large ? 16384 : 8192;
+  plan.RT = st == Store::F64 ? 16 : 32;
+  sigma_items(g, large ? 32 : plan.RT, wide ? 8 : 4, items, plan.npan_v);
+  plan.unit_items = (int)items.size();
+  sigma_items(g, plan.RT, wide ? 8 : 4, items, plan.npan_v);
+  plan.nitems = (int)items.size();
 }
 
 template <typename T, int CC, int RT, int OCC>
@@ -617,22 +610,35 @@ static hipError_t run_group(const GroupMember* m, int n, hipStream_t s) {
 }
 
 hipError_t launch_sigma_group_bf16(const GroupMember* m, int n, hipStream_t s);
-hipError_t launch_sigma_group_f64(const GroupMember* m, int n, hipStream_t s);
-hipError_t launch_sigma_f64(const Geometry& g, const SigmaPlan& plan, const SigmaLaunch& la,
-                            hipStream_t s);
 
-hipError_t launch_sigma_group(const GroupMember* m, int n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  if (n > GROUP_MAX) return hipErrorInvalidValue;
+static hipError_t launch_sigma_group_fused(const GroupMember* m, int n, hipStream_t s) {
   const int variant = m[0].plan->variant;
   for (int i = 1; i < n; ++i)
     if (m[i].plan->variant != variant || m[i].la.nprod != m[0].la.nprod) return hipErrorInvalidValue;
   switch (variant) {
     case 1: return run_group<double, 8, 16, 2>(m, n, s);
-    case 5: return launch_sigma_group_f64(m, n, s);
     case 4: return run_group<float, 16, 32, 2>(m, n, s);
     default: return launch_sigma_group_bf16(m, n, s);
   }
+}
+
+// Members of the two-product form each fill the chip: one after the other, then the rest as one
+// grid.
+hipError_t launch_sigma_group(const GroupMember* m, int n, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  if (n > GROUP_MAX) return hipErrorInvalidValue;
+  GroupMember rest[GROUP_MAX];
+  int nrest = 0;
+  for (int i = 0; i < n; ++i) {
+    const SigmaLaunch& la = m[i].la;
+    if (mm_plan(m[i].st, mm_geometry(*m[i].g), la.k, la.nsplit * la.k).nslot == 0) {
+      rest[nrest++] = m[i];
+      continue;
+    }
+    const hipError_t e = launch_sigma(*m[i].g, m[i].st, *m[i].plan, la, s);
+    if (e != hipSuccess) return e;
+  }
+  return nrest ? launch_sigma_group_fused(rest, nrest, s) : hipSuccess;
 }
 
 hipError_t launch_sigma_bf16(const Geometry& g, const SigmaPlan& plan, const SigmaLaunch& la,
@@ -640,9 +646,12 @@ hipError_t launch_sigma_bf16(const Geometry& g, const SigmaPlan& plan, const Sig
 
 hipError_t launch_sigma(const Geometry& g, Store st, const SigmaPlan& plan, const SigmaLaunch& la,
                         hipStream_t s) {
+  const MmGeometry mg = mm_geometry(g);
+  const MmPlan m = mm_plan(st, mg, la.k, la.nsplit * la.k);
+  if (m.nslot > 0)
+    return launch_sigma_mm(st, mg, m, la.L, la.L, la.ZT, la.Sp, la.ws_slots, la.k, s);
   switch (plan.variant) {
     case 1: return run_sandwich<double, 8, 16, 2>(g, plan, la, s);
-    case 5: return launch_sigma_f64(g, plan, la, s);
     case 4: return run_sandwich<float, 16, 32, 2>(g, plan, la, s);
     default: return launch_sigma_bf16(g, plan, la, s);
   }

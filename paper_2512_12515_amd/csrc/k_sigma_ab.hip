@@ -26,6 +26,7 @@
 #include "internal.h"
 #include "sigma_common.h"
 #include "sigma_bf16.h"
+#include "sigma_mm.h"
 
 namespace pprpa {
 namespace {
@@ -273,25 +274,20 @@ void k_sandwich_ab(const T* __restrict__ La, const T* __restrict__ Lb,
 // pair energies (+ for vv, - for oo pairs).
 template <typename T>
 __global__ __launch_bounds__(256) void k_epilogue_ab(const double* __restrict__ z, int64_t n,
-                                                     int64_t nvv, int nvb, int nob, int nvpa,
-                                                     int nvpb, int nmopb, const T* __restrict__ Qp,
-                                                     int nsplit, int64_t split_stride,
-                                                     int64_t q_stride,
+                                                     int64_t nvv, int nvb, int nob, int nmopb,
+                                                     const T* __restrict__ Qp, SigmaSums q,
                                                      const double* __restrict__ epair,
                                                      double* __restrict__ sigma) {
   const int kv = blockIdx.y;
   const int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t e = e0 < n ? e0 : n - 1;  // clamped: every thread's loads stay in bounds
-  int r, c;
-  if (e < nvv) {
-    r = (int)(e / nvb);
-    c = (int)(e % nvb);
-  } else {
-    const int64_t s = e - nvv;
-    r = nvpa + (int)(s / nob);
-    c = nvpb + (int)(s % nob);
-  }
-  const T* Q = Qp + (int64_t)kv * q_stride + (int64_t)r * nmopb + c;
+  const bool virt = e < nvv;
+  const int64_t s = virt ? e : e - nvv;
+  const int r = (int)(s / (virt ? nvb : nob)), c = (int)(s % (virt ? nvb : nob));
+  const T* Q = virt ? Qp + kv * q.vec + (int64_t)r * nmopb + c
+                    : Qp + q.off_o + kv * q.vec_o + (int64_t)r * q.ld_o + c;
+  const int nsplit = virt ? q.nsplit : q.nsplit_o;
+  const int64_t split_stride = virt ? q.split : q.split_o;
   double acc = 0.0;
 #pragma unroll 8
   for (int t = 0; t < nsplit; ++t) acc += (double)Q[t * split_stride];
@@ -556,7 +552,10 @@ hipError_t launch_unpack_ab(const AbGeometry& g, Store st, const double* z, int 
 
 hipError_t launch_sigma_ab(const AbGeometry& g, Store st, int nprod, const SigmaPlan& plan,
                            const void* La, const void* Lb, const void* ZT, size_t zplane, void* Qp,
-                           int k, int nsplit, hipStream_t s) {
+                           int k, int nsplit, int64_t ws_slots, hipStream_t s) {
+  const MmGeometry mg = mm_geometry(g);
+  const MmPlan m = mm_plan(st, mg, k, nsplit * k);
+  if (m.nslot > 0) return launch_sigma_mm(st, mg, m, La, Lb, ZT, Qp, ws_slots, k, s);
   AbParams p;
   p.nvta = g.nvta;
   p.ncta = g.ncta;
@@ -597,22 +596,16 @@ hipError_t launch_sigma_ab(const AbGeometry& g, Store st, int nprod, const Sigma
   return hipGetLastError();
 }
 
-hipError_t launch_epilogue_ab(const AbGeometry& g, Store st, const double* z, int k,
-                              const void* Qp, int nsplit, const double* epair, double* sigma,
-                              hipStream_t s) {
+hipError_t launch_epilogue_ab(const AbGeometry& g, const SigmaSums& q, const double* z, int k,
+                              const void* Qp, const double* epair, double* sigma, hipStream_t s) {
   if (k <= 0) return hipSuccess;
-  const int64_t q_stride = (int64_t)g.nmopa * g.nmopb;
   dim3 grid((unsigned)((g.n + 255) / 256), (unsigned)k);
-  if (st == Store::F64)
+  if (q.st == Store::F64)
     hipLaunchKernelGGL(k_epilogue_ab<double>, grid, dim3(256), 0, s, z, g.n, g.nvv, g.nvb, g.nob,
-                       g.nvpa, g.nvpb, g.nmopb, (const double*)Qp, nsplit, (int64_t)k * q_stride,
-                       q_stride, epair, sigma);
-  else if (st == Store::F32 || st == Store::BF16)
-    hipLaunchKernelGGL(k_epilogue_ab<float>, grid, dim3(256), 0, s, z, g.n, g.nvv, g.nvb, g.nob,
-                       g.nvpa, g.nvpb, g.nmopb, (const float*)Qp, nsplit, (int64_t)k * q_stride,
-                       q_stride, epair, sigma);
+                       g.nmopb, (const double*)Qp, q, epair, sigma);
   else
-    return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_epilogue_ab<float>, grid, dim3(256), 0, s, z, g.n, g.nvv, g.nvb, g.nob,
+                       g.nmopb, (const float*)Qp, q, epair, sigma);
   return hipGetLastError();
 }
 

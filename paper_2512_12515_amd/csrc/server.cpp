@@ -17,11 +17,12 @@
 //   form the next group (continuous batching), so the groups grow with the load; a small-class
 //   launch is held for up to HOLD_US while other small solves of the same variant are still in
 //   their Davidson phases, so that solves running side by side fall into one grid. Solves of
-//   different kernel variants (sigma precision, FP64 kernel by size) cannot share a grid; the
+//   different kernel variants (sigma precision, BF16x6 kernel by size) cannot share a grid; the
 //   variant whose waiting block has waited longest goes next, so no request is overtaken by more
-//   than one launch per other variant of its class. A member's work units are
-//   those of a launch of its own (same decomposition, same partial-sum buffer), so its results do
-//   not depend on the mix it was served in.
+//   than one launch per other variant of its class. Members whose product runs as two matrix
+//   products, each enough for the chip, go one after the other ahead of the rest's grid. A member's
+//   work units are those of a launch of its own (same decomposition, same partial-sum buffer), so
+//   its results do not depend on the mix it was served in.
 // * Finished solves copy out their roots, release their reservation and slot, and wake the
 //   admission thread.
 #include <algorithm>
@@ -276,11 +277,12 @@ bool launch_group(pprpa_server* S, std::vector<Request*>& grp, int cls,
     la.Sp = c->Sp;
     la.k = k;
     la.nsplit = ns[i];
+    la.ws_slots = c->sp_slots;
     la.npan_v = c->plan.npan_v;
     la.plane = c->plane;
     la.zplane = c->zplane;
     la.nprod = c->nprod;
-    m[i] = GroupMember{&c->g, &c->plan, la};
+    m[i] = GroupMember{&c->g, c->st, &c->plan, la};
     const Geometry& g = c->g;
     flops += 4.0 * g.naux * (double)(g.nv + g.no) * ((double)g.nv * g.nv + (double)g.no * g.no) * k;
   }
@@ -307,8 +309,9 @@ bool launch_group(pprpa_server* S, std::vector<Request*>& grp, int cls,
     Solver& sv = *r->sv;
     const int64_t n = c->g.n;
     if (hipStreamWaitEvent(c->stream, tg.b, 0) != hipSuccess) return false;
-    if (launch_epilogue(c->g, c->st, sv.w.V + (size_t)sv.sig_m0 * n, sv.sig_k, c->Sp, ns[i], c->ptab,
-                        c->epair, sv.w.SV + (size_t)sv.sig_m0 * n, c->stream) != hipSuccess)
+    const SigmaSums q = sigma_sums(c->g, c->st, sv.sig_k, ns[i]);
+    if (launch_epilogue(c->g, q, sv.w.V + (size_t)sv.sig_m0 * n, sv.sig_k, c->Sp, c->epair,
+                        sv.w.SV + (size_t)sv.sig_m0 * n, c->stream) != hipSuccess)
       return false;
     r->unpacked = false;
     sv.sigma_done(false);
