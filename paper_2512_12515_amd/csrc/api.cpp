@@ -758,18 +758,21 @@ pprpa_status corr_energy_run(pprpa_ctx* c, double* work, pprpa_corr_energy* out)
   double* dout = work + 3 * (size_t)n * n;  // 4 doubles, then 3 ints
   int* dinfo = (int*)(dout + 4);
   double* hp = c->pinned;
-  // one workgroup up to order 96, many above (the no-allocation entry point goes to 512)
-  hipError_t le = n <= DENSE_ONE_WG_MAX ? launch_pencil_energy(c->M, (int)n, nvv, c->mu2, dout, work, dinfo, c->stream)
-                           : launch_pencil_energy_mw(c->M, (int)n, nvv, c->mu2, dout, work, dinfo,
-                                                     c->stream);
-  if (le == hipSuccess) le = hipMemcpyAsync(hp, dout, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-  if (le == hipSuccess) le = hipMemcpyAsync(hp + 4, dinfo, 3 * sizeof(int), hipMemcpyDeviceToHost, c->stream);
-  if (le == hipSuccess) le = hipStreamSynchronize(c->stream);
-  if (le != hipSuccess) {
-    set_error("correlation energy: %s", hipGetErrorString(le));
-    return PPRPA_EDEVICE;
-  }
   const int* info = (const int*)(hp + 4);
+  for (int one = 1; one >= 0; --one) {
+    // one workgroup up to order 96, many above (the no-allocation entry point goes to 512)
+    hipError_t le = n <= DENSE_ONE_WG_MAX ? launch_pencil_energy(c->M, (int)n, nvv, c->mu2, dout, work, dinfo, c->stream)
+                             : launch_pencil_energy_mw(c->M, (int)n, nvv, c->mu2, dout, work, dinfo,
+                                                       one, c->stream);
+    if (le == hipSuccess) le = hipMemcpyAsync(hp, dout, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    if (le == hipSuccess) le = hipMemcpyAsync(hp + 4, dinfo, 3 * sizeof(int), hipMemcpyDeviceToHost, c->stream);
+    if (le == hipSuccess) le = hipStreamSynchronize(c->stream);
+    if (le != hipSuccess) {
+      set_error("correlation energy: %s", hipGetErrorString(le));
+      return PPRPA_EDEVICE;
+    }
+    if (info[0] != 4) break;
+  }
   if (info[0] == 1) {
     set_error("M - 2 mu W is not positive definite");
     return PPRPA_ENONDEF;

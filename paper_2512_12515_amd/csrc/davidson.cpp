@@ -501,22 +501,25 @@ pprpa_status Solver::run_direct() {
                              direct_pencil_mw_work(m, nroot_)}),
                    (size_t)nroot_ * 64, &w));
   double* hp = c_->pinned;
-  PPRPA_HIP(launch_metric_matrix(w.Ws_, n, nvv, s));
-  if (m <= DENSE_ONE_WG_MAX)  // W as a dense matrix: the Davidson pencil solver on the whole problem
-    PPRPA_HIP(launch_pencil(c_->M, w.Ws_, m, m, c_->mu2, nroot_, nroot_, a_.channel, w.omega,
-                            w.Cc, nroot_, w.pwork, w.info, s));
-  else  // W diagonal, many workgroups
-    PPRPA_HIP(launch_direct_pencil_mw(c_->M, m, nvv, c_->mu2, nroot_, a_.channel, w.omega, w.Cc,
-                                      nroot_, w.pwork, w.info, s));
-  PPRPA_HIP(launch_transpose(w.Cc, nroot_, m, nroot_, w.Z, n, s));
-  PPRPA_HIP(launch_combine(c_->M, n, m, w.Cc, nroot_, nroot_, n, 1.0, 0.0, w.SZ, n, s));
-  PPRPA_HIP(launch_residual(w.Z, w.SZ, n, nroot_, n, nvv, w.omega, w.R, w.part, 64, s));
-  PPRPA_HIP(launch_reduce_norms(w.part, 64, nroot_, w.rnorm, s));
-  PPRPA_HIP(hipMemcpyAsync(hp, w.omega, nroot_ * sizeof(double), hipMemcpyDeviceToHost, s));
-  PPRPA_HIP(hipMemcpyAsync(hp + 64, w.rnorm, nroot_ * sizeof(double), hipMemcpyDeviceToHost, s));
-  PPRPA_HIP(hipMemcpyAsync(hp + 128, w.info, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
-  PPRPA_HIP(hipStreamSynchronize(s));
   const int* info = (const int*)(hp + 128);
+  if (m <= DENSE_ONE_WG_MAX) PPRPA_HIP(launch_metric_matrix(w.Ws_, n, nvv, s));
+  for (int one = 1; one >= 0; --one) {
+    if (m <= DENSE_ONE_WG_MAX)  // W as a dense matrix: the Davidson pencil solver on the whole problem
+      PPRPA_HIP(launch_pencil(c_->M, w.Ws_, m, m, c_->mu2, nroot_, nroot_, a_.channel, w.omega,
+                              w.Cc, nroot_, w.pwork, w.info, s));
+    else  // W diagonal, many workgroups
+      PPRPA_HIP(launch_direct_pencil_mw(c_->M, m, nvv, c_->mu2, nroot_, a_.channel, w.omega, w.Cc,
+                                        nroot_, w.pwork, w.info, one, s));
+    PPRPA_HIP(launch_transpose(w.Cc, nroot_, m, nroot_, w.Z, n, s));
+    PPRPA_HIP(launch_combine(c_->M, n, m, w.Cc, nroot_, nroot_, n, 1.0, 0.0, w.SZ, n, s));
+    PPRPA_HIP(launch_residual(w.Z, w.SZ, n, nroot_, n, nvv, w.omega, w.R, w.part, 64, s));
+    PPRPA_HIP(launch_reduce_norms(w.part, 64, nroot_, w.rnorm, s));
+    PPRPA_HIP(hipMemcpyAsync(hp, w.omega, nroot_ * sizeof(double), hipMemcpyDeviceToHost, s));
+    PPRPA_HIP(hipMemcpyAsync(hp + 64, w.rnorm, nroot_ * sizeof(double), hipMemcpyDeviceToHost, s));
+    PPRPA_HIP(hipMemcpyAsync(hp + 128, w.info, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+    PPRPA_HIP(hipStreamSynchronize(s));
+    if (info[0] != 4) break;  // (4: the one-launch reduction gave up, again without it)
+  }
   if (info[0] == 1) {
     set_error("M - 2 mu W is not positive definite");
     return PPRPA_ENONDEF;

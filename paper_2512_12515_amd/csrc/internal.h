@@ -222,13 +222,13 @@ hipError_t launch_pencil(const double* Ms, const double* Ws, int ldm, int m, dou
 // info: [0] 0 ok / 1 not definite, [1] pp roots, [2] hh roots. work: 3 m^2 doubles.
 hipError_t launch_pencil_energy(const double* M, int m, int64_t nvv, double mu2, double* out,
                                 double* work, int* info, hipStream_t s);
-// The same outputs as launch_pencil_energy for 2 <= m <= DENSE_ENERGY_MAX on many workgroups
+// The same outputs as launch_pencil_energy for 32 <= m <= DENSE_ENERGY_MAX on many workgroups
 // (blocked Cholesky, S = L^T W L, Householder tridiagonal form, bisection; k_dense_mw.hip).
-// work: pencil_energy_mw_work(m) doubles.
-size_t pencil_energy_mw_work(int n);
+// work: 3 m^2 doubles. one_launch: the tridiagonal form by launch_tridiag where it fits; info[0] = 4
+// when its workgroups lost one another (solve again without).
 hipError_t launch_pencil_energy_mw(const double* M, int m, int64_t nvv, double mu2, double* out,
-                                   double* work, int* info, hipStream_t s);
-// Direct solve of the dense pencil (M, W), W = diag(+1 for i < nvv, -1), for 3 <= m <=
+                                   double* work, int* info, bool one_launch, hipStream_t s);
+// Direct solve of the dense pencil (M, W), W = diag(+1 for i < nvv, -1), for 32 <= m <=
 // DENSE_SOLVE_MAX on many workgroups (the chain of launch_pencil_energy_mw keeping its
 // reflections, multisection for the wanted eigenvalues, inverse iteration, back-transformation,
 // L^T z = u): the outputs of launch_pencil (nret = nroot). work: direct_pencil_mw_work(m, nroot)
@@ -236,7 +236,16 @@ hipError_t launch_pencil_energy_mw(const double* M, int m, int64_t nvv, double m
 size_t direct_pencil_mw_work(int n, int nroot);
 hipError_t launch_direct_pencil_mw(const double* M, int m, int64_t nvv, double mu2, int nroot,
                                    int channel, double* omega, double* Cout, int ldc,
-                                   double* work, int* info, hipStream_t s);
+                                   double* work, int* info, bool one_launch, hipStream_t s);
+// Tridiagonal form (d, e) of nmat symmetric n x n matrices S (k_tridiag.hip), 3 <= n <= TRIDIAG_MAX
+// where tridiag_fits; X: exchange buffer of nmat tridiag_exchange(n) doubles. beta_keep (nmat = 1): the reflection
+// vectors stay in the rows of S right of the diagonal. *abort_flag: 0, or 1 when the workgroups
+// lost one another (the outputs are then not usable).
+constexpr int TRIDIAG_MAX = 1088;
+bool tridiag_fits(int n);
+size_t tridiag_exchange(int n);
+hipError_t launch_tridiag(double* S, int n, int nmat, double* X, double* d, double* e,
+                          double* beta_keep, int* abort_flag, hipStream_t s);
 // NTO weights and two-electron density blocks of k packed roots Z [k][ldz] (nv, no <= 512):
 // X [k][nv][nv], Y [k][no][no] (triangular amplitude matrices), Gx, Gy (their T^T T, destroyed),
 // Dv = X X^T + X^T X, Do = -(Y Y^T + Y^T Y) (may be null), lam_p [k][nv], lam_h [k][no]

@@ -28,21 +28,19 @@
 //      L^T z = u by blocked back substitution and z scaled by sqrt|lambda|, so that
 //      z^T W z = |lambda| u^T S^-1 u = sign(lambda) (S^-1 = L^-1 W L^-T).
 // Every reduction runs in a fixed order: the result is bitwise repeatable.
+#include <algorithm>
+
 #include "internal.h"
+#include "wave.h"
 
 namespace pprpa {
 namespace {
 
 constexpr int CB = 32;  // Cholesky block and tile edge
 
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // sum over the workgroup (every thread gets it); red: blockDim.x / 64 doubles of LDS
 __device__ __forceinline__ double wg_sum(double v, double* red) {
-  v = wave_sum(v);
+  v = wave_total(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double r = red[0];
@@ -74,8 +72,8 @@ __device__ __forceinline__ void tri_pair(int x, int* r, int* c) {
   *c = x - i * (i + 1) / 2;
 }
 
-__global__ void k_mw_init(int* flag) {
-  if (threadIdx.x == 0) flag[0] = 0;
+__global__ void k_mw_init(int* flag, int* lost) {
+  if (threadIdx.x == 0) flag[0] = lost[0] = 0;
 }
 
 // K = M - mu2 W, mu2 = 2 mu, W = diag(+1 for i < nvv, -1)
@@ -87,49 +85,56 @@ __global__ __launch_bounds__(256) void k_mw_shift(const double* __restrict__ M, 
   K[e] = M[e] - (i == j ? mu2 * (i < nvv ? 1.0 : -1.0) : 0.0);
 }
 
-// Cholesky of the diagonal block at (j0, j0), b = min(CB, n - j0) rows, in place (lower); a
-// non-positive pivot sets flag.
-__global__ __launch_bounds__(256) void k_mw_chol_diag(double* __restrict__ K, int n, int j0,
-                                                      int* __restrict__ flag) {
-  __shared__ double a[CB][CB + 1];
-  const int b = min(CB, n - j0);
-  for (int e = threadIdx.x; e < CB * CB; e += 256) {
-    const int r = e / CB, c = e % CB;
-    a[r][c] = (r < b && c < b) ? K[(int64_t)(j0 + r) * n + j0 + c] : 0.0;
+// Cholesky of the diagonal block at (j0, j0) (b = min(CB, n - j0) rows, lower) and the panel below
+// it: row i >= j0 + CB solves x L_jj^T = K[i][j0 .. j0 + CB) by forward substitution, a row per
+// thread. Every workgroup factorises the block itself (wave 0, a row per lane, columns in
+// registers, the pivot column broadcast by lane reads: with the panel 14 us, against 22 for the block
+// in LDS with three barriers a column and 9 for the panel in a launch of its own), workgroup 0 writes it to D (CB x CB, row-major); the block in K is
+// overwritten by the next kernel, since other workgroups still read it here. A non-positive pivot
+// sets flag.
+__global__ __launch_bounds__(256) void k_mw_chol_panel(double* __restrict__ K, int n, int j0,
+                                                       double* __restrict__ D,
+                                                       int* __restrict__ flag) {
+  __shared__ double l[CB][CB + 2], inv[CB];  // l by columns
+  const int b = min(CB, n - j0), t = threadIdx.x;
+  if (t < 64) {
+    double a[CB];
+    const int r = min(t, b - 1);
+#pragma unroll
+    for (int c = 0; c < CB; ++c) a[c] = t < b && c <= r ? K[(int64_t)(j0 + r) * n + j0 + c] : 0.0;
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      if (c < b) {  // uniform
+        const double piv = lane_value(a[c], c);
+        if (!(piv > 0.0) && t == 0 && blockIdx.x == 0) flag[0] = 1;
+        // 1 / sqrt by the hardware's estimate and two Newton steps
+        double ic = __builtin_amdgcn_rsq(piv);
+        ic = piv > 0.0 ? ic : 0.0;
+        ic = ic * __builtin_fma(-0.5 * piv * ic, ic, 1.5);
+        ic = ic * __builtin_fma(-0.5 * piv * ic, ic, 1.5);
+        double dc = piv * ic;
+        dc = __builtin_fma(__builtin_fma(-dc, dc, piv), 0.5 * ic, dc);
+        if (!(piv > 0.0)) dc = 0.0;
+        a[c] = t == c ? dc : (t > c ? a[c] * ic : 0.0);
+        if (t == 0) inv[c] = ic;
+#pragma unroll
+        for (int k = c + 1; k < CB; ++k) {
+          const double lk = lane_value(a[c], k);  // 0 for k >= b
+          a[k] = __builtin_fma(-a[c], lk, a[k]);  // (above the diagonal: not used)
+        }
+      }
+    }
+    if (t < CB) {
+#pragma unroll
+      for (int c = 0; c < CB; ++c) {
+        l[c][t] = a[c];
+        if (blockIdx.x == 0) D[t * CB + c] = a[c];
+      }
+      if (t >= b) inv[t] = 0.0;
+    }
   }
   __syncthreads();
-  for (int c = 0; c < b; ++c) {
-    if (threadIdx.x == 0) {
-      const double piv = a[c][c];
-      if (!(piv > 0.0)) flag[0] = 1;
-      a[c][c] = sqrt(fmax(piv, 0.0));
-    }
-    __syncthreads();
-    const double dc = a[c][c];
-    for (int r = c + 1 + threadIdx.x; r < b; r += 256) a[r][c] = dc > 0.0 ? a[r][c] / dc : 0.0;
-    __syncthreads();
-    for (int e = threadIdx.x; e < CB * CB; e += 256) {
-      const int r = e / CB, t = e % CB;
-      if (r > c && r < b && t > c && t <= r) a[r][t] -= a[r][c] * a[t][c];
-    }
-    __syncthreads();
-  }
-  for (int e = threadIdx.x; e < CB * CB; e += 256) {
-    const int r = e / CB, c = e % CB;
-    if (r < b && c <= r) K[(int64_t)(j0 + r) * n + j0 + c] = a[r][c];
-  }
-}
-
-// Panel below the diagonal block: row i >= j0 + CB solves x L_jj^T = K[i][j0 .. j0 + CB) by
-// forward substitution (a thread per row).
-__global__ __launch_bounds__(256) void k_mw_chol_trsm(double* __restrict__ K, int n, int j0) {
-  __shared__ double l[CB][CB + 1];
-  for (int e = threadIdx.x; e < CB * CB; e += 256) {
-    const int r = e / CB, c = e % CB;
-    l[r][c] = c <= r ? K[(int64_t)(j0 + r) * n + j0 + c] : 0.0;
-  }
-  __syncthreads();
-  const int i = j0 + CB + blockIdx.x * 256 + threadIdx.x;
+  const int i = j0 + CB + blockIdx.x * 256 + t;
   if (i >= n) return;
   double x[CB];
   double* row = K + (int64_t)i * n + j0;
@@ -137,19 +142,34 @@ __global__ __launch_bounds__(256) void k_mw_chol_trsm(double* __restrict__ K, in
   for (int c = 0; c < CB; ++c) x[c] = row[c];
 #pragma unroll
   for (int c = 0; c < CB; ++c) {
-    double s = x[c];
+    x[c] *= inv[c];
 #pragma unroll
-    for (int t = 0; t < c; ++t) s -= x[t] * l[c][t];
-    x[c] = l[c][c] > 0.0 ? s / l[c][c] : 0.0;
+    for (int k = c + 1; k < CB; ++k) x[k] -= x[c] * l[c][k];
   }
 #pragma unroll
   for (int c = 0; c < CB; ++c) row[c] = x[c];
 }
 
+// The factorised diagonal block into K (the last block, which has no panel below).
+__global__ __launch_bounds__(256) void k_mw_chol_store(double* __restrict__ K, int n, int j0,
+                                                       const double* __restrict__ D) {
+  for (int e = threadIdx.x; e < CB * CB; e += 256) {
+    const int r = e / CB, c = e % CB;
+    if (j0 + r < n && c <= r) K[(int64_t)(j0 + r) * n + j0 + c] = D[e];
+  }
+}
+
 // Trailing update of the lower triangle right of the panel: K[i][k] -= sum_t L[i][j0+t] L[k][j0+t]
-// for j0 + CB <= k <= i, one 32 x 32 tile (I >= J) per workgroup, four elements per thread.
-__global__ __launch_bounds__(256) void k_mw_chol_update(double* __restrict__ K, int n, int j0) {
+// for j0 + CB <= k <= i, one 32 x 32 tile (I >= J) per workgroup, four elements per thread; the first
+// workgroup also stores the factorised diagonal block D.
+__global__ __launch_bounds__(256) void k_mw_chol_update(double* __restrict__ K, int n, int j0,
+                                                        const double* __restrict__ D) {
   __shared__ double pi[CB][CB + 1], pk[CB][CB + 1];
+  if (blockIdx.x == 0)
+    for (int e = threadIdx.x; e < CB * CB; e += 256) {
+      const int r = e / CB, c = e % CB;
+      if (c <= r) K[(int64_t)(j0 + r) * n + j0 + c] = D[e];
+    }
   int I, J;
   tri_pair(blockIdx.x, &I, &J);
   const int r0 = j0 + CB + I * CB, c0 = j0 + CB + J * CB;
@@ -254,7 +274,7 @@ __global__ __launch_bounds__(256) void k_mw_hh_matvec(const double* __restrict__
   const double* row = S + (int64_t)(k + 1 + r) * n + k + 1;
   double s = 0.0;
   for (int j = lane; j < m; j += 64) s += row[j] * v[j];
-  s = wave_sum(s);
+  s = wave_total(s);
   if (lane == 0) p[r] = scal[0] * s;
 }
 
@@ -295,7 +315,7 @@ __global__ __launch_bounds__(256) void k_mw_hh_update(double* __restrict__ S, in
     if (j >= 1) ss += nv * nv;
   }
   if (!next) return;
-  const double nrm2 = wave_sum(ss);
+  const double nrm2 = wave_total(ss);
   x0 = __shfl(x0, 1, 64);
   dg = __shfl(dg, 0, 64);
   const double nrm = sqrt(nrm2);
@@ -312,27 +332,64 @@ __global__ __launch_bounds__(256) void k_mw_hh_update(double* __restrict__ S, in
   }
 }
 
-__device__ __forceinline__ int mw_sturm_below(const double* __restrict__ d,
-                                              const double* __restrict__ e, int n, double x,
-                                              double tiny) {
+// Eigenvalues of T below x: sign changes of the leading minors p_i = (d_i - x) p_{i-1} -
+// e_{i-1}^2 p_{i-2}. t2: (d_i, e_{i-1}^2) of T scaled by a power of two to norm 1 .. 2 (x scaled
+// alike), filled up with (4, 0), which change no sign, to a multiple of 8 and by 8 more (a block is
+// read ahead). Each minor takes the sign of exact arithmetic on a T perturbed by roundings, as the
+// ratios p_i / p_{i-1} do, but a step of the chain is one FMA and not a division. |p| grows by at
+// most 2^3 and shrinks by at most 2^100 a step: rescaled every 8 steps. A minor of 0 may count with
+// either sign, as the next one has the sign opposite to the one before it; only where the
+// off-diagonal element after it is 0 as well, all that follow are 0: such a block is taken again with
+// the 0 as just past the sign change.
+__device__ __forceinline__ int mw_sturm_below(const double* __restrict__ t2, int n, double x) {
+  double p0 = 0.0, p1 = 1.0;
   int cnt = 0;
-  double q = d[0] - x;
-  if (q < 0.0) ++cnt;
-  for (int i = 1; i < n; ++i) {
-    if (fabs(q) < tiny) q = -tiny;
-    q = (d[i] - x) - e[i - 1] * e[i - 1] / q;
-    if (q < 0.0) ++cnt;
+  auto step = [&](double di, double e2) __attribute__((always_inline)) {
+    const double p2 = __builtin_fma(di - x, p1, -(e2 * p0));
+    cnt += (int)((unsigned)(__double2hiint(p2) ^ __double2hiint(p1)) >> 31);
+    p0 = p1;
+    p1 = p2;
+  };
+  double a[16], c[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) a[u] = t2[u];
+  for (int i = 0; i < n; i += 8) {
+    const double s0 = p0, s1 = p1;
+    const int sc = cnt;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) c[u] = a[u];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) a[u] = t2[2 * i + 16 + u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) step(c[2 * u], c[2 * u + 1]);
+    if (p0 == 0.0 && p1 == 0.0) {
+      p0 = s0;
+      p1 = s1 == 0.0 ? copysign(0x1p-100, s1) : s1;
+      cnt = sc;
+      for (int u = i; u < i + 8; ++u) {
+        step(t2[2 * u], t2[2 * u + 1]);
+        if (p1 == 0.0) {
+          cnt += (int)((unsigned)(__double2hiint(p1) ^ ~__double2hiint(p0)) >> 31);
+          p1 = p0 * -0x1p-100;
+        }
+      }
+    }
+    const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
+    p0 = ldexp(p0, -ex);
+    p1 = ldexp(p1, -ex);
   }
   return cnt;
 }
 
-// The last two diagonal and the last off-diagonal entry, then the Gershgorin interval of T:
-// bnd[0] = lower, bnd[1] = upper, bnd[2] = a norm of T (one workgroup).
+// The last two diagonal and the last off-diagonal entry (from S, if given), then the Gershgorin interval of T:
+// bnd[0] = lower, bnd[1] = upper, bnd[2] = a norm of T, and t2: T
+// scaled by bnd[3], a power of two, as mw_sturm_below takes it (one workgroup).
 __global__ __launch_bounds__(1024) void k_mw_bounds(const double* __restrict__ S, int n,
                                                     double* __restrict__ d, double* __restrict__ e,
-                                                    double* __restrict__ bnd) {
+                                                    double* __restrict__ bnd,
+                                                    double* __restrict__ t2) {
   __shared__ double red[16];
-  if (threadIdx.x == 0) {
+  if (S && threadIdx.x == 0) {
     if (n >= 2) {
       d[n - 2] = S[(int64_t)(n - 2) * n + n - 2];
       e[n - 2] = S[(int64_t)(n - 1) * n + n - 2];
@@ -353,34 +410,45 @@ __global__ __launch_bounds__(1024) void k_mw_bounds(const double* __restrict__ S
     bnd[1] = ghi;
     bnd[2] = fmax(gn, 1e-300);
   }
+  int ex = 0;
+  frexp(fmin(fmax(gn, 1e-300), 1e300), &ex);
+  const double sc = ldexp(1.0, 1 - ex);
+  if (threadIdx.x == 0) bnd[3] = sc;
+  for (int i = threadIdx.x; i < (n + 15) / 8 * 8; i += 1024) {
+    const double ei = i > 0 && i < n ? e[i - 1] * sc : 0.0;
+    t2[2 * i] = i < n ? d[i] * sc : 4.0;
+    t2[2 * i + 1] = ei * ei;
+  }
 }
 
-// Eigenvalue idx (ascending) of T, 16 lanes each: per round the lanes take the Sturm count at 16
+// Eigenvalue idx (ascending) of T, L lanes each: per round the lanes take the Sturm count at L
 // evenly spaced interior points of the bracket, which shrinks to the two neighbouring points that
-// enclose the index (reduced over the 16 lanes by shuffles), until its width is at the rounding
-// level. A wave runs until its four brackets are done.
-__global__ __launch_bounds__(256) void k_mw_bisect(const double* __restrict__ d,
-                                                   const double* __restrict__ e, int n,
+// enclose the index (reduced over the lanes by shuffles), until its width is at the rounding level.
+// A wave runs until its brackets are done. A whole wave an eigenvalue (9 rounds instead of 13) as
+// long as their waves fit the chip together (n <= 4096). n = 1071: 0.32 ms, against 1.43 with 16
+// lanes and the ratios' divisions.
+template <int L>
+__global__ __launch_bounds__(256) void k_mw_bisect(const double* __restrict__ t2, int n,
                                                    const double* __restrict__ bnd,
                                                    double* __restrict__ lam) {
   const int gid = blockIdx.x * 256 + threadIdx.x;
-  const int idx = gid >> 4, g = gid & 15;
-  const double tnorm = bnd[2];
+  const int idx = gid / L, g = gid % L;
+  const double tnorm = bnd[2], sc = bnd[3];
   const double tiny = 1e-300 + 2.2e-16 * tnorm * 1e-8;
   double lo = bnd[0] - 1e-12 * tnorm, hi = bnd[1] + 1e-12 * tnorm;
   bool done = idx >= n;
   for (int round = 0; round < 64; ++round) {
     if (!done) done = !(hi - lo > 4.4e-16 * fmax(fabs(lo), fabs(hi)) + tiny);
     if (__all(done)) break;
-    const double x = lo + (hi - lo) * ((double)(g + 1) / 17.0);
+    const double x = lo + (hi - lo) * ((double)(g + 1) / (L + 1.0));
     double xl = -1e300, xh = 1e300;
     if (!done && x > lo && x < hi) {
-      if (mw_sturm_below(d, e, n, x, tiny) <= idx)
+      if (mw_sturm_below(t2, n, x * sc) <= idx)
         xl = x;
       else
         xh = x;
     }
-    for (int off = 8; off > 0; off >>= 1) {
+    for (int off = L / 2; off > 0; off >>= 1) {
       xl = fmax(xl, __shfl_xor(xl, off, 64));
       xh = fmin(xh, __shfl_xor(xh, off, 64));
     }
@@ -430,18 +498,10 @@ __global__ __launch_bounds__(1024) void k_mw_sums(const double* __restrict__ M, 
     out[1] = -SHH - TC;
     out[2] = TA;
     out[3] = TC;
-    info[0] = flag[0] ? 1 : 0;
+    info[0] = info[1] ? 4 : (flag[0] ? 1 : 0);  // (info[1]: the reduction's lost flag, until here)
     info[1] = (int)NPP;
     info[2] = (int)NHH;
   }
-}
-
-// Number of eigenvalues of T below 0 (the hh roots) -> cnt[0].
-__global__ void k_mw_count(const double* __restrict__ d, const double* __restrict__ e, int n,
-                           const double* __restrict__ bnd, int* __restrict__ cnt) {
-  if (threadIdx.x != 0) return;
-  const double tiny = 1e-300 + 2.2e-16 * bnd[2] * 1e-8;
-  cnt[0] = mw_sturm_below(d, e, n, 0.0, tiny);
 }
 
 // Ascending index of wanted root j: pp (channel 0) the j-th eigenvalue above 0, hh the j-th below
@@ -455,20 +515,22 @@ __device__ __forceinline__ int mw_wanted(int j, int nbelow, int n, int channel) 
 // 256 evenly spaced interior points of the bracket, which shrinks to the two neighbouring points
 // that enclose the root's index, until its width is at the rounding level. lam[j] = 0 for a root
 // the channel does not have.
-__global__ __launch_bounds__(256) void k_mw_select(const double* __restrict__ d,
-                                                   const double* __restrict__ e, int n,
+__global__ __launch_bounds__(256) void k_mw_select(const double* __restrict__ t2, int n,
                                                    const double* __restrict__ bnd,
-                                                   const int* __restrict__ cnt, int channel,
+                                                   int* __restrict__ cnt, int channel,
                                                    const int* __restrict__ flag,
                                                    double* __restrict__ lam) {
   __shared__ double red[4];
   const int j = blockIdx.x, t = threadIdx.x;
-  const int idx = mw_wanted(j, cnt[0], n, channel);
+  // eigenvalues below 0 (the hh roots)
+  const int nbelow = mw_sturm_below(t2, n, 0.0);
+  if (j == 0 && t == 0) cnt[0] = nbelow;
+  const int idx = mw_wanted(j, nbelow, n, channel);
   if (flag[0] || idx < 0) {
     if (t == 0) lam[j] = 0.0;
     return;
   }
-  const double tnorm = bnd[2];
+  const double tnorm = bnd[2], sc = bnd[3];
   const double tiny = 1e-300 + 2.2e-16 * tnorm * 1e-8;
   double lo = bnd[0] - 1e-12 * tnorm, hi = bnd[1] + 1e-12 * tnorm;
   for (int round = 0; round < 64; ++round) {
@@ -476,7 +538,7 @@ __global__ __launch_bounds__(256) void k_mw_select(const double* __restrict__ d,
     const double x = lo + (hi - lo) * ((double)(t + 1) / 257.0);
     double xl = -1e300, xh = 1e300;
     if (x > lo && x < hi) {
-      if (mw_sturm_below(d, e, n, x, tiny) <= idx)
+      if (mw_sturm_below(t2, n, x * sc) <= idx)
         xl = x;
       else
         xh = x;
@@ -490,10 +552,13 @@ __global__ __launch_bounds__(256) void k_mw_select(const double* __restrict__ d,
   if (t == 0) lam[j] = 0.5 * (lo + hi);
 }
 
-// Eigenvector of T at lam[j] by inverse iteration (thread j): three solves of (T - lam I) y = b
-// by Gaussian elimination with partial pivoting (the fill-in on a second superdiagonal), y
-// normalised after each; the start vector a fixed pseudo-random sequence per root. Y [nsel][n]
-// (zero for a root the channel does not have); U [nsel][3][n] elimination scratch.
+// Eigenvector of T at lam[j] by inverse iteration (lane j): three solves of (T - lam I) y = b by
+// Gaussian elimination with partial pivoting (the fill-in on a second superdiagonal), y normalised
+// after each; the start vector a fixed pseudo-random sequence per root. The elimination's rows and
+// the vectors are kept lane-fastest (W [4][n][64]: inverse pivots, the two superdiagonals, y), so
+// that each step is one line, and a step's only division is its pivot's (a row per root and a
+// division in each substitution step took 391 us at n = 225). Y [nsel][n] gets the vectors (zero
+// for a root the channel does not have).
 __global__ __launch_bounds__(64) void k_mw_inviter(const double* __restrict__ d,
                                                    const double* __restrict__ e, int n,
                                                    const double* __restrict__ bnd,
@@ -501,71 +566,147 @@ __global__ __launch_bounds__(64) void k_mw_inviter(const double* __restrict__ d,
                                                    const int* __restrict__ flag,
                                                    const double* __restrict__ lam, int nsel,
                                                    double* __restrict__ Y,
-                                                   double* __restrict__ U) {
+                                                   double* __restrict__ W) {
   const int j = threadIdx.x;
-  if (j >= nsel) return;
-  double* y = Y + (size_t)j * n;
-  if (flag[0] || mw_wanted(j, cnt[0], n, channel) < 0) {
-    for (int i = 0; i < n; ++i) y[i] = 0.0;
-    return;
-  }
-  double* U0 = U + (size_t)j * 3 * n;
-  double* U1 = U0 + n;
-  double* U2 = U1 + n;
-  const double th = lam[j];
+  const bool has = j < nsel && !flag[0] && mw_wanted(j, cnt[0], n, channel) >= 0;
+  double* I0 = W + j;
+  double* U1 = I0 + (size_t)64 * n;
+  double* U2 = U1 + (size_t)64 * n;
+  double* y = U2 + (size_t)64 * n;
+  const double th = has ? lam[j] : 2.0 * bnd[2];
   const double pert = 2.2e-16 * bnd[2];
   unsigned long long h = 0xD1B54A32D192ED03ull * (unsigned long long)(j + 1);
   for (int i = 0; i < n; ++i) {
     h ^= h >> 31;
     h *= 0x9FB21C651E98DF25ull;
     h ^= h >> 29;
-    y[i] = 0.5 + (double)(h >> 11) * (1.0 / 9007199254740992.0);
+    y[64 * (size_t)i] = 0.5 + (double)(h >> 11) * (1.0 / 9007199254740992.0);
   }
+  double scale = 1.0;  // of the last solve's y
   for (int pass = 0; pass < 3; ++pass) {
     // forward elimination: row i holds (a_d, a_u, a_u2 | rhs) after the pivots above it
-    double a_d = d[0] - th, a_u = n > 1 ? e[0] : 0.0, a_u2 = 0.0, rhs = y[0];
+    double a_d = d[0] - th, a_u = n > 1 ? e[0] : 0.0, a_u2 = 0.0, rhs = y[0] * scale;
+    double nextb = n > 1 ? y[64] : 0.0;
+#pragma unroll 4
     for (int i = 0; i + 1 < n; ++i) {
       const double b_l = e[i], b_d = d[i + 1] - th, b_u = i + 2 < n ? e[i + 1] : 0.0;
-      const double rb = y[i + 1];
-      if (fabs(a_d) >= fabs(b_l)) {
-        const double piv = fabs(a_d) < pert ? (a_d < 0.0 ? -pert : pert) : a_d;
-        const double l = b_l / piv;
-        U0[i] = piv;
-        U1[i] = a_u;
-        U2[i] = a_u2;
-        y[i] = rhs;
-        a_d = b_d - l * a_u;
-        a_u = b_u - l * a_u2;
-        a_u2 = 0.0;
-        rhs = rb - l * rhs;
-      } else {  // rows i and i + 1 exchanged
-        const double l = a_d / b_l;
-        U0[i] = b_l;
-        U1[i] = b_d;
-        U2[i] = b_u;
-        y[i] = rb;
-        a_d = a_u - l * b_d;
-        a_u = a_u2 - l * b_u;
-        a_u2 = 0.0;
-        rhs = rhs - l * rb;
-      }
+      const double rb = nextb * scale;
+      nextb = i + 2 < n ? y[64 * (size_t)(i + 2)] : 0.0;
+      const bool swap = fabs(a_d) < fabs(b_l);  // rows i and i + 1 exchanged
+      const double pv = swap ? b_l : a_d;
+      const double piv = fabs(pv) < pert ? (pv < 0.0 ? -pert : pert) : pv;
+      const double ip = 1.0 / piv;
+      const double l = (swap ? a_d : b_l) * ip;
+      const double p1 = swap ? b_d : a_u, p2 = swap ? b_u : a_u2, pr = swap ? rb : rhs;
+      const double s0 = swap ? a_u : b_d, s1 = swap ? a_u2 : b_u, sr = swap ? rhs : rb;
+      I0[64 * (size_t)i] = ip;
+      U1[64 * (size_t)i] = p1;
+      U2[64 * (size_t)i] = p2;
+      y[64 * (size_t)i] = pr;
+      a_d = s0 - l * p1;
+      a_u = s1 - l * p2;
+      a_u2 = 0.0;
+      rhs = sr - l * pr;
     }
     if (fabs(a_d) < pert) a_d = a_d < 0.0 ? -pert : pert;
-    U0[n - 1] = a_d;
-    U1[n - 1] = 0.0;
-    U2[n - 1] = 0.0;
-    y[n - 1] = rhs;
-    double y1 = 0.0, y2 = 0.0, nrm2 = 0.0;
-    for (int i = n - 1; i >= 0; --i) {
-      const double v = (y[i] - U1[i] * y1 - U2[i] * y2) / U0[i];
-      y[i] = v;
-      y2 = y1;
-      y1 = v;
+    double y1 = 0.0, y2 = rhs / a_d, nrm2 = y2 * y2;  // y2: the element just found
+    y[64 * (size_t)(n - 1)] = y2;
+#pragma unroll 4
+    for (int i = n - 2; i >= 0; --i) {
+      const double v = (y[64 * (size_t)i] - U1[64 * (size_t)i] * y2 - U2[64 * (size_t)i] * y1) *
+                       I0[64 * (size_t)i];
+      y[64 * (size_t)i] = v;
+      y1 = y2;
+      y2 = v;
       nrm2 += v * v;
     }
-    const double inv = 1.0 / sqrt(nrm2);
-    for (int i = 0; i < n; ++i) y[i] *= inv;
+    scale = 1.0 / sqrt(nrm2);
   }
+  if (j >= nsel) return;
+  for (int i = 0; i < n; ++i) Y[(size_t)j * n + i] = has ? y[64 * (size_t)i] * scale : 0.0;
+}
+
+// The same for n <= INVITER_LDS, a workgroup (one lane of it) per root with T, the elimination and
+// the vector in LDS: the elimination runs once, the next two solves take its multipliers, and a
+// step's chain is two FMAs: 87 us at n = 225 and 0.40 ms at n = 1071, against 391 us and 1.87 ms with
+// the vectors in memory.
+constexpr int INVITER_LDS = 2048;
+__global__ __launch_bounds__(64) void k_mw_inviter_lds(const double* __restrict__ d,
+                                                       const double* __restrict__ e, int n,
+                                                       const double* __restrict__ bnd,
+                                                       const int* __restrict__ cnt, int channel,
+                                                       const int* __restrict__ flag,
+                                                       const double* __restrict__ lam,
+                                                       double* __restrict__ Y) {
+  __shared__ double dS[INVITER_LDS], eS[INVITER_LDS], ip[INVITER_LDS], u1[INVITER_LDS],
+      u2[INVITER_LDS], li[INVITER_LDS], y[INVITER_LDS];
+  __shared__ unsigned char sw[INVITER_LDS];
+  __shared__ double last;
+  const int j = blockIdx.x, lane = threadIdx.x;
+  if (flag[0] || mw_wanted(j, cnt[0], n, channel) < 0) {
+    for (int i = lane; i < n; i += 64) Y[(size_t)j * n + i] = 0.0;
+    return;
+  }
+  const double th = lam[j], pert = 2.2e-16 * bnd[2];
+  for (int i = lane; i < n; i += 64) {
+    dS[i] = d[i] - th;
+    eS[i] = i + 1 < n ? e[i] : 0.0;
+    // the start vector: a mix of root and row
+    unsigned long long h = 0xD1B54A32D192ED03ull * ((unsigned long long)j * 8192 + i + 1);
+    h ^= h >> 31;
+    h *= 0x9FB21C651E98DF25ull;
+    h ^= h >> 29;
+    y[i] = 0.5 + (double)(h >> 11) * (1.0 / 9007199254740992.0);
+  }
+  __syncthreads();
+  if (lane == 0) {
+    double a_d = dS[0], a_u = eS[0], a_u2 = 0.0;
+#pragma unroll 4
+    for (int i = 0; i + 1 < n; ++i) {
+      const double b_l = eS[i], b_d = dS[i + 1], b_u = eS[i + 1];
+      const bool swap = fabs(a_d) < fabs(b_l);  // rows i and i + 1 exchanged
+      const double pv = swap ? b_l : a_d;
+      const double r = fast_rcp(fabs(pv) < pert ? (pv < 0.0 ? -pert : pert) : pv);
+      const double l = (swap ? a_d : b_l) * r;
+      const double p1 = swap ? b_d : a_u, p2 = swap ? b_u : a_u2;
+      const double s0 = swap ? a_u : b_d, s1 = swap ? a_u2 : b_u;
+      ip[i] = r;
+      u1[i] = p1;
+      u2[i] = p2;
+      li[i] = l;
+      sw[i] = swap;
+      a_d = s0 - l * p1;
+      a_u = s1 - l * p2;
+      a_u2 = 0.0;
+    }
+    if (fabs(a_d) < pert) a_d = a_d < 0.0 ? -pert : pert;
+    double scale = 1.0;
+    for (int pass = 0; pass < 3; ++pass) {
+      double rhs = y[0] * scale;
+#pragma unroll 8
+      for (int i = 0; i + 1 < n; ++i) {
+        const double rb = y[i + 1] * scale, l = li[i];
+        const bool swap = sw[i];
+        const double pr = swap ? rb : rhs;
+        y[i] = pr;
+        rhs = (swap ? rhs : rb) - l * pr;
+      }
+      double y1 = 0.0, y2 = rhs / a_d, nrm2 = y2 * y2;
+      y[n - 1] = y2;
+#pragma unroll 8
+      for (int i = n - 2; i >= 0; --i) {
+        const double v = (y[i] - u2[i] * y1 - u1[i] * y2) * ip[i];
+        y[i] = v;
+        y1 = y2;
+        y2 = v;
+        nrm2 += v * v;
+      }
+      scale = 1.0 / sqrt(nrm2);
+    }
+    last = scale;
+  }
+  __syncthreads();
+  for (int i = lane; i < n; i += 64) Y[(size_t)j * n + i] = y[i] * last;
 }
 
 // Vectors of nearly equal eigenvalues (|lam_i - lam_j| <= 1e-7 |T|) orthonormalised in order
@@ -600,6 +741,100 @@ __global__ __launch_bounds__(1024) void k_mw_orth(int n, const double* __restric
   }
 }
 
+// Root j for n <= 64 Q, one wave each, the vector in its registers (element 64 q + lane in register
+// q): u = H_0 H_1 ... H_{n-3} y (reflection k in row k of S right of the diagonal, beta[k]), L^T z =
+// u from the last row up, and the outputs of k_mw_vectors. A reflection is a dot product by DPP moves
+// and an update, a row of the substitution a lane read and an update, with no barrier, and the next
+// rows are loaded ahead: 91 us at n = 225 against 674 with a workgroup a root (1.17 ms against 3.75
+// at n = 1071, the rows' way from the last-level cache to one compute unit).
+template <int Q>
+__global__ __launch_bounds__(64) void k_mw_back(const double* __restrict__ K,
+                                                const double* __restrict__ S,
+                                                const double* __restrict__ beta, int n,
+                                                const int* __restrict__ cnt, int channel,
+                                                const int* __restrict__ flag,
+                                                const int* __restrict__ lost,
+                                                const double* __restrict__ lam,
+                                                const double* __restrict__ Y, double mu2,
+                                                double* __restrict__ omega,
+                                                double* __restrict__ Cout, int ldc,
+                                                int* __restrict__ info) {
+  constexpr int AHEAD = Q <= 4 ? 8 : Q <= 20 ? 4 : 2;
+  const int j = blockIdx.x, lane = threadIdx.x;
+  const int bad = flag[0], nb = cnt[0];
+  const int npos = bad ? 0 : (channel == 0 ? n - nb : nb);
+  if (j == 0 && lane == 0) {
+    info[0] = lost[0] ? 4 : (bad ? 1 : (npos < (int)gridDim.x ? 2 : 0));
+    info[1] = npos;
+    info[2] = 0;
+  }
+  if (bad || j >= npos) {
+    if (lane == 0) omega[j] = 0.0;
+    for (int r = lane; r < n; r += 64) Cout[(size_t)r * ldc + j] = 0.0;
+    return;
+  }
+  const double lj = lam[j];
+  if (lane == 0) omega[j] = mu2 + lj;
+  const double* yj = Y + (size_t)j * n;
+  double y[Q], v[AHEAD][Q], b[AHEAD];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) y[q] = 64 * q + lane < n ? yj[64 * q + lane] : 0.0;
+  auto refl = [&](int k, double (&vk)[Q], double& bk) __attribute__((always_inline)) {
+    bk = k >= 0 ? beta[k] : 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int r = 64 * q + lane;
+      vk[q] = k >= 0 && r > k && r < n ? S[(size_t)k * n + r] : 0.0;
+    }
+  };
+#pragma unroll
+  for (int a = 0; a < AHEAD; ++a) refl(n - 3 - a, v[a], b[a]);
+  for (int k = n - 3; k >= 0; k -= AHEAD) {
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a) {  // (past reflection 0: zero vectors)
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) s += v[a][q] * y[q];
+      const double bs = b[a] * wave_total(s);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) y[q] -= bs * v[a][q];
+      refl(k - a - AHEAD, v[a], b[a]);
+    }
+  }
+#pragma unroll
+  for (int jq = Q - 1; jq >= 0; --jq) {  // rows 64 jq + 63 .. 64 jq
+    if (64 * jq >= n) continue;          // uniform
+    auto row = [&](int l, double (&vk)[Q]) __attribute__((always_inline)) {
+      const int c = 64 * jq + l;
+#pragma unroll
+      for (int q = 0; q <= jq; ++q)
+        vk[q] = l >= 0 && 64 * q + lane < c ? K[(size_t)c * n + 64 * q + lane] : 0.0;
+    };
+    const int l0 = min(63, n - 1 - 64 * jq);
+    const size_t rr = 64 * jq + min(lane, l0);
+    const double dinv = 1.0 / K[rr * n + rr];
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a) row(l0 - a, v[a]);
+    for (int l1 = l0; l1 >= 0; l1 -= AHEAD) {
+#pragma unroll
+      for (int a = 0; a < AHEAD; ++a) {
+        const int l = l1 - a;
+        if (l >= 0) {  // uniform
+          const double z = lane_value(y[jq] * dinv, l);
+#pragma unroll
+          for (int q = 0; q <= jq; ++q) y[q] -= v[a][q] * z;
+          y[jq] = lane == l ? z : y[jq];
+        }
+        row(l - AHEAD, v[a]);
+      }
+    }
+  }
+  const double sc = sqrt(fabs(lj));
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (64 * q + lane < n) Cout[(size_t)(64 * q + lane) * ldc + j] = y[q] * sc;
+}
+
 // Root j (a workgroup each; the vector in LDS, element r owned by thread r mod 256): u = H_0 H_1
 // ... H_{n-3} y (reflection k kept in row k of S right of the diagonal, beta[k]), then L^T z = u
 // by back substitution in 32-row blocks (the block's triangle within one wave, the rows above it
@@ -611,6 +846,7 @@ __global__ __launch_bounds__(256) void k_mw_vectors(const double* __restrict__ K
                                                     const double* __restrict__ beta, int n,
                                                     const int* __restrict__ cnt, int channel,
                                                     const int* __restrict__ flag,
+                                                    const int* __restrict__ lost,
                                                     const double* __restrict__ lam,
                                                     const double* __restrict__ Y, double mu2,
                                                     double* __restrict__ omega,
@@ -623,7 +859,7 @@ __global__ __launch_bounds__(256) void k_mw_vectors(const double* __restrict__ K
   const int nb = cnt[0];
   const int npos = bad ? 0 : (channel == 0 ? n - nb : nb);
   if (j == 0 && t == 0) {
-    info[0] = bad ? 1 : (npos < (int)gridDim.x ? 2 : 0);
+    info[0] = lost[0] ? 4 : (bad ? 1 : (npos < (int)gridDim.x ? 2 : 0));
     info[1] = npos;
     info[2] = 0;
   }
@@ -660,7 +896,7 @@ __global__ __launch_bounds__(256) void k_mw_vectors(const double* __restrict__ K
         const int r = t + 256 * q;
         if (r > k && r < n) s += vc[q] * y[r];
       }
-      s = wave_sum(s);
+      s = wave_total(s);
       double* rb = red[ph];
       ph ^= 1;
       if ((t & 63) == 0) rb[t >> 6] = s;
@@ -715,25 +951,35 @@ __global__ __launch_bounds__(256) void k_mw_vectors(const double* __restrict__ K
 // Steps 1-4 (K, its Cholesky factor, S = L^T W L, the tridiagonal form (d, e) with the bounds
 // of its spectrum) on stream s. v2: 2 n (the reflection vectors of two steps), bsc: 5 doubles
 // ([0], [1] beta of even and odd steps, [2 .. 4] the bounds); beta_keep: n doubles or null (keep
-// the reflections in the rows of S); flag: zeroed, then set when K is not positive definite.
-static void mw_reduce(const double* M, int n, int64_t nvv, double mu2, double* K, double* S,
-                      double* v2, double* p, double* d, double* e, double* bsc,
-                      double* beta_keep, int* flag, hipStream_t s) {
+// the reflections in the rows of S); X: tridiag_exchange(n) doubles (the tridiagonal form in one
+// launch up to TRIDIAG_MAX; may overlap K where it is not needed after S), or null; flag, lost: zeroed, then set
+// when K is not positive definite, or the reduction's workgroups lost one another.
+static hipError_t mw_reduce(const double* M, int n, int64_t nvv, double mu2, double* K, double* S,
+                            double* X, double* v2, double* p, double* d, double* e, double* bsc,
+                            double* beta_keep, int* flag, int* lost, hipStream_t s) {
   const size_t nn = (size_t)n * n;
-  hipLaunchKernelGGL(k_mw_init, dim3(1), dim3(64), 0, s, flag);
+  hipLaunchKernelGGL(k_mw_init, dim3(1), dim3(64), 0, s, flag, lost);
   hipLaunchKernelGGL(k_mw_shift, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, M, n, nvv,
                      mu2, K);
-  for (int j0 = 0; j0 < n; j0 += CB) {
-    hipLaunchKernelGGL(k_mw_chol_diag, dim3(1), dim3(256), 0, s, K, n, j0, flag);
-    const int rest = n - j0 - CB;
-    if (rest > 0) {
-      hipLaunchKernelGGL(k_mw_chol_trsm, dim3((rest + 255) / 256), dim3(256), 0, s, K, n, j0);
-      const int nt = (rest + CB - 1) / CB;
-      hipLaunchKernelGGL(k_mw_chol_update, dim3(nt * (nt + 1) / 2), dim3(256), 0, s, K, n, j0);
-    }
+  for (int j0 = 0; j0 < n; j0 += CB) {  // S, not formed yet, holds the diagonal block
+    const int rest = std::max(0, n - j0 - CB);
+    hipLaunchKernelGGL(k_mw_chol_panel, dim3(std::max(1, (rest + 255) / 256)), dim3(256), 0, s, K, n,
+                       j0, S, flag);
+    const int nt = (rest + CB - 1) / CB;
+    if (rest > 0)
+      hipLaunchKernelGGL(k_mw_chol_update, dim3(nt * (nt + 1) / 2), dim3(256), 0, s, K, n, j0, S);
+    else
+      hipLaunchKernelGGL(k_mw_chol_store, dim3(1), dim3(256), 0, s, K, n, j0, S);
   }
   const int ntile = (n + CB - 1) / CB;
   hipLaunchKernelGGL(k_mw_sym, dim3(ntile * (ntile + 1) / 2), dim3(256), 0, s, K, n, nvv, S);
+  if (X && tridiag_fits(n)) {
+    const hipError_t rc = launch_tridiag(S, n, 1, X, d, e, beta_keep, lost, s);
+    if (rc != hipSuccess) return rc;
+    hipLaunchKernelGGL(k_mw_bounds, dim3(1), dim3(1024), 0, s, (const double*)nullptr, n, d, e, bsc + 2,
+                       v2);
+    return hipGetLastError();
+  }
   if (n > 2)
     hipLaunchKernelGGL(k_mw_hh_vec, dim3(1), dim3(1024), 0, s, S, n, 0, v2, bsc, d, e, beta_keep);
   for (int k = 0; k + 2 < n; ++k) {
@@ -744,65 +990,90 @@ static void mw_reduce(const double* M, int n, int64_t nvv, double mu2, double* K
     hipLaunchKernelGGL(k_mw_hh_update, dim3((m + 3) / 4), dim3(256), 0, s, S, n, k, vk, bsc + c, p,
                        beta_keep ? 1 : 0, vn, bsc + (1 - c), d, e, beta_keep);
   }
-  hipLaunchKernelGGL(k_mw_bounds, dim3(1), dim3(1024), 0, s, S, n, d, e, bsc + 2);
+  hipLaunchKernelGGL(k_mw_bounds, dim3(1), dim3(1024), 0, s, S, n, d, e, bsc + 2, v2);
+  return hipGetLastError();
 }
 
-size_t pencil_energy_mw_work(int n) { return 2 * (size_t)n * n + 6 * (size_t)n + 8; }
 
 hipError_t launch_pencil_energy_mw(const double* M, int n, int64_t nvv, double mu2, double* out,
-                                   double* work, int* info, hipStream_t s) {
-  if (n < 2 || n > DENSE_ENERGY_MAX) return hipErrorInvalidValue;
+                                   double* work, int* info, bool one_launch, hipStream_t s) {
+  if (n < 32 || n > DENSE_ENERGY_MAX) return hipErrorInvalidValue;
   const size_t nn = (size_t)n * n;
-  double* K = work;
-  double* S = K + nn;
-  double* v2 = S + nn;
+  double* S = work;
+  double* v2 = S + nn;  // with p, from k_mw_bounds on: 2 (n + 15) elements
   double* p = v2 + 2 * (size_t)n;
   double* d = p + n;
   double* e = d + n;
   double* lam = e + n;
   double* bsc = lam + n;  // [0], [1] beta, [2 .. 4] Gershgorin bounds and norm
-  int* flag = info;       // info[0] doubles as the not-definite flag until the last kernel
-  mw_reduce(M, n, nvv, mu2, K, S, v2, p, d, e, bsc, nullptr, flag, s);
-  hipLaunchKernelGGL(k_mw_bisect, dim3((unsigned)((16 * (size_t)n + 255) / 256)), dim3(256), 0, s,
-                     d, e, n, bsc + 2, lam);
+  double* K = bsc + 8;    // and, once S is formed, with the rest of work the exchange buffer
+  double* X = one_launch && K + tridiag_exchange(n) <= work + 3 * nn ? K : nullptr;
+  int* flag = info;  // info[0], info[1] double as the flags until the last kernel
+  const hipError_t rc = mw_reduce(M, n, nvv, mu2, K, S, X, v2, p, d, e, bsc, nullptr, flag, info + 1, s);
+  if (rc != hipSuccess) return rc;
+  if (n <= 4096)
+    hipLaunchKernelGGL(k_mw_bisect<64>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, v2, n,
+                       bsc + 2, lam);
+  else
+    hipLaunchKernelGGL(k_mw_bisect<16>, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, v2, n,
+                       bsc + 2, lam);
   hipLaunchKernelGGL(k_mw_sums, dim3(1), dim3(1024), 0, s, M, n, nvv, mu2, lam, flag, out, info);
   return hipGetLastError();
 }
 
 size_t direct_pencil_mw_work(int n, int nroot) {
-  return 2 * (size_t)n * n + 6 * (size_t)n + 4 * (size_t)nroot * n + 64 + 8 + 8;
+  return (n <= TRIDIAG_MAX ? tridiag_exchange(n) : 0) + 2 * (size_t)n * n + 6 * (size_t)n + (size_t)nroot * n +
+         256 * (size_t)n + 64 + 8 + 8;
 }
 
 hipError_t launch_direct_pencil_mw(const double* M, int n, int64_t nvv, double mu2, int nroot,
                                    int channel, double* omega, double* Cout, int ldc,
-                                   double* work, int* info, hipStream_t s) {
-  if (n < 3 || n > DENSE_SOLVE_MAX || nroot < 1 || nroot > 64 || nroot > n || ldc < nroot ||
+                                   double* work, int* info, bool one_launch, hipStream_t s) {
+  if (n < 32 || n > DENSE_SOLVE_MAX || nroot < 1 || nroot > 64 || nroot > n || ldc < nroot ||
       (channel != 0 && channel != 1))
     return hipErrorInvalidValue;
   const size_t nn = (size_t)n * n;
   double* K = work;
   double* S = K + nn;
-  double* v2 = S + nn;
+  double* X = n <= TRIDIAG_MAX ? S + nn : nullptr;
+  double* v2 = S + nn + (X ? tridiag_exchange(n) : 0);
   double* p = v2 + 2 * (size_t)n;
   double* d = p + n;
   double* e = d + n;
   double* beta = e + n;
   double* Y = beta + n;
-  double* U = Y + (size_t)nroot * n;
-  double* lam = U + 3 * (size_t)nroot * n;  // 64
-  double* bsc = lam + 64;                   // [0], [1] beta, [2 .. 4] bounds
-  int* cnt = (int*)(bsc + 8);               // [0] eigenvalues below 0
-  int* flag = cnt + 1;                      // K not positive definite
-  mw_reduce(M, n, nvv, mu2, K, S, v2, p, d, e, bsc, beta, flag, s);
-  hipLaunchKernelGGL(k_mw_count, dim3(1), dim3(64), 0, s, d, e, n, bsc + 2, cnt);
-  hipLaunchKernelGGL(k_mw_select, dim3(nroot), dim3(256), 0, s, d, e, n, bsc + 2, cnt, channel,
-                     flag, lam);
-  hipLaunchKernelGGL(k_mw_inviter, dim3(1), dim3(64), 0, s, d, e, n, bsc + 2, cnt, channel, flag,
-                     lam, nroot, Y, U);
+  double* W = Y + (size_t)nroot * n;
+  double* lam = W + 256 * (size_t)n;  // 64
+  double* bsc = lam + 64;             // [0], [1] beta, [2 .. 4] bounds
+  int* cnt = (int*)(bsc + 8);         // [0] eigenvalues below 0
+  int* flag = cnt + 1;                // K not positive definite
+  int* lost = cnt + 2;                // the reduction's workgroups lost one another
+  const hipError_t rc = mw_reduce(M, n, nvv, mu2, K, S, one_launch ? X : nullptr, v2, p, d, e, bsc,
+                                  beta, flag, lost, s);
+  if (rc != hipSuccess) return rc;
+  hipLaunchKernelGGL(k_mw_select, dim3(nroot), dim3(256), 0, s, v2, n, bsc + 2, cnt, channel, flag,
+                     lam);
+  if (n <= INVITER_LDS)
+    hipLaunchKernelGGL(k_mw_inviter_lds, dim3(nroot), dim3(64), 0, s, d, e, n, bsc + 2, cnt, channel,
+                       flag, lam, Y);
+  else
+    hipLaunchKernelGGL(k_mw_inviter, dim3(1), dim3(64), 0, s, d, e, n, bsc + 2, cnt, channel, flag,
+                       lam, nroot, Y, W);
   hipLaunchKernelGGL(k_mw_orth, dim3(1), dim3(1024), 0, s, n, bsc + 2, cnt, channel, flag, lam,
                      nroot, Y);
-  hipLaunchKernelGGL(k_mw_vectors, dim3(nroot), dim3(256), 0, s, K, S, beta, n, cnt, channel, flag,
-                     lam, Y, mu2, omega, Cout, ldc, info);
+  // one wave a root as long as its vector and the rows ahead fit the registers
+  if (n <= 64 * 4)
+    hipLaunchKernelGGL(k_mw_back<4>, dim3(nroot), dim3(64), 0, s, K, S, beta, n, cnt, channel, flag,
+                       lost, lam, Y, mu2, omega, Cout, ldc, info);
+  else if (n <= 64 * 17)
+    hipLaunchKernelGGL(k_mw_back<17>, dim3(nroot), dim3(64), 0, s, K, S, beta, n, cnt, channel, flag,
+                       lost, lam, Y, mu2, omega, Cout, ldc, info);
+  else if (n <= 64 * 32)
+    hipLaunchKernelGGL(k_mw_back<32>, dim3(nroot), dim3(64), 0, s, K, S, beta, n, cnt, channel, flag,
+                       lost, lam, Y, mu2, omega, Cout, ldc, info);
+  else
+    hipLaunchKernelGGL(k_mw_vectors, dim3(nroot), dim3(256), 0, s, K, S, beta, n, cnt, channel, flag,
+                       lost, lam, Y, mu2, omega, Cout, ldc, info);
   return hipGetLastError();
 }
 
