@@ -1024,8 +1024,9 @@ static pprpa_status nto_ab(pprpa_ctx* c, int k, const double* z, int on_device, 
   const size_t dv = (size_t)k * ((size_t)nva * nva + (size_t)nvb * nvb);
   const size_t dov = (size_t)k * ((size_t)noa * noa + (size_t)nob * nob);
   const size_t lv = (size_t)k * nva, lo = (size_t)k * noa;
-  // z (when on the host), Gx, Gy, Dv, Do, lam_p, lam_h
-  const size_t total = (on_device ? 0 : zv) + gv + go + dv + dov + lv + lo;
+  // z (when on the host), Gx, Gy, Dv, Do, lam_p, lam_h, workspace, flags
+  const size_t wl = nto_work(k, nva, noa);
+  const size_t total = (on_device ? 0 : zv) + gv + go + dv + dov + lv + lo + wl + 1;
   double* buf = nullptr;
   hipError_t e = hipMalloc((void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
   if (e != hipSuccess) {
@@ -1044,18 +1045,28 @@ static pprpa_status nto_ab(pprpa_ctx* c, int k, const double* z, int on_device, 
   double* Dv = p; p += dv;
   double* Do = p; p += dov;
   double* lp = p; p += lv;
-  double* lh = p;
+  double* lh = p; p += lo;
+  double* wk = p; p += wl;
+  int* lost = (int*)p;
   hipStream_t s = c->stream;
   hipError_t le = hipSuccess;
   if (!on_device) le = hipMemcpyAsync((void*)dz, z, zv * sizeof(double), hipMemcpyHostToDevice, s);
-  if (le == hipSuccess)
-    le = launch_nto_ab(dz, g.n, k, nva, nvb, noa, nob, Gx, Gy, Dv, Do, lp, lh, s);
-  if (le == hipSuccess) le = hipMemcpyAsync(lam_p, lp, lv * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (le == hipSuccess && lo) le = hipMemcpyAsync(lam_h, lh, lo * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (le == hipSuccess && d_vv) le = hipMemcpyAsync(d_vv, Dv, dv * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (le == hipSuccess && d_oo && dov)
-    le = hipMemcpyAsync(d_oo, Do, dov * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (le == hipSuccess) le = hipStreamSynchronize(s);
+  const bool sv = nto_spectra(nva), so = nto_spectra(noa);
+  int* hl = (int*)c->pinned;
+  for (int one = 1; le == hipSuccess && one >= 0; --one) {
+    hl[0] = hl[1] = 0;
+    le = launch_nto_ab(dz, g.n, k, nva, nvb, noa, nob, Gx, Gy, Dv, Do, lp, lh, wk, lost, one, s);
+    if (le == hipSuccess) le = hipMemcpyAsync(lam_p, lp, lv * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && lo) le = hipMemcpyAsync(lam_h, lh, lo * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && d_vv) le = hipMemcpyAsync(d_vv, Dv, dv * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && d_oo && dov)
+      le = hipMemcpyAsync(d_oo, Do, dov * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && one && sv) le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && one && so)
+      le = hipMemcpyAsync(hl + 1, lost + 1, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess) le = hipStreamSynchronize(s);
+    if (!hl[0] && !hl[1]) break;  // (else: the one-launch reduction gave up, again without it)
+  }
   (void)hipFree(buf);
   if (le != hipSuccess) {
     set_error("NTO analysis: %s", hipGetErrorString(le));
@@ -1085,8 +1096,9 @@ pprpa_status pprpa_nto(pprpa_ctx* c, int32_t k, const double* z, int32_t on_devi
   PPRPA_HIP(hipSetDevice(c->device));
   const size_t zv = (size_t)k * g.n, mv = (size_t)k * g.nv * g.nv, mo = (size_t)k * g.no * g.no;
   const size_t lv = (size_t)k * g.nv, lo = (size_t)k * g.no;
-  // z (when on the host), X, Y, Gx, Gy, Dv, Do, lam_p, lam_h
-  const size_t total = (on_device ? 0 : zv) + 3 * mv + 3 * mo + lv + lo;
+  // z (when on the host), X, Y, Gx, Gy, Dv, Do, lam_p, lam_h, workspace, flags
+  const size_t wl = nto_work(k, g.nv, g.no);
+  const size_t total = (on_device ? 0 : zv) + 3 * mv + 3 * mo + lv + lo + wl + 1;
   double* buf = nullptr;
   hipError_t e = hipMalloc((void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
   if (e != hipSuccess) {
@@ -1107,17 +1119,28 @@ pprpa_status pprpa_nto(pprpa_ctx* c, int32_t k, const double* z, int32_t on_devi
   double* Gy = p; p += mo;
   double* Do = p; p += mo;
   double* lp = p; p += lv;
-  double* lh = p;
+  double* lh = p; p += lo;
+  double* wk = p; p += wl;
+  int* lost = (int*)p;
   hipStream_t s = c->stream;
   hipError_t le = hipSuccess;
   if (!on_device) le = hipMemcpyAsync((void*)dz, z, zv * sizeof(double), hipMemcpyHostToDevice, s);
-  if (le == hipSuccess)
-    le = launch_nto(dz, g.n, k, g, c->ptab, X, Y, Gx, Gy, Dv, Do, lp, lh, s);
-  if (le == hipSuccess) le = hipMemcpyAsync(lam_p, lp, lv * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (le == hipSuccess && lo) le = hipMemcpyAsync(lam_h, lh, lo * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (le == hipSuccess && d_vv) le = hipMemcpyAsync(d_vv, Dv, mv * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (le == hipSuccess && d_oo && mo) le = hipMemcpyAsync(d_oo, Do, mo * sizeof(double), hipMemcpyDeviceToHost, s);
-  if (le == hipSuccess) le = hipStreamSynchronize(s);
+  const bool sv = nto_spectra(g.nv), so = nto_spectra(g.no);
+  int* hl = (int*)c->pinned;
+  for (int one = 1; le == hipSuccess && one >= 0; --one) {
+    hl[0] = hl[1] = 0;
+    le = launch_nto(dz, g.n, k, g, c->ptab, X, Y, Gx, Gy, Dv, Do, lp, lh, wk, lost, one, s);
+    if (le == hipSuccess) le = hipMemcpyAsync(lam_p, lp, lv * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && lo) le = hipMemcpyAsync(lam_h, lh, lo * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && d_vv) le = hipMemcpyAsync(d_vv, Dv, mv * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && d_oo && mo)
+      le = hipMemcpyAsync(d_oo, Do, mo * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && one && sv) le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && one && so)
+      le = hipMemcpyAsync(hl + 1, lost + 1, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess) le = hipStreamSynchronize(s);
+    if (!hl[0] && !hl[1]) break;  // (else: the one-launch reduction gave up, again without it)
+  }
   (void)hipFree(buf);
   if (le != hipSuccess) {
     set_error("NTO analysis: %s", hipGetErrorString(le));

@@ -246,20 +246,31 @@ bool tridiag_fits(int n);
 size_t tridiag_exchange(int n);
 hipError_t launch_tridiag(double* S, int n, int nmat, double* X, double* d, double* e,
                           double* beta_keep, int* abort_flag, hipStream_t s);
+// Eigenvalues, descending and clamped at zero, of nmat symmetric n x n matrices S (destroyed) where
+// tridiag_fits(n): lam [nmat][n]. work: spectra_work(n, nmat) doubles; *lost as *abort_flag above.
+size_t spectra_work(int n, int nmat);
+hipError_t launch_spectra(double* S, int n, int nmat, double* lam, double* work, int* lost,
+                          hipStream_t s);
 // NTO weights and two-electron density blocks of k packed roots Z [k][ldz] (nv, no <= 512):
 // X [k][nv][nv], Y [k][no][no] (triangular amplitude matrices), Gx, Gy (their T^T T, destroyed),
 // Dv = X X^T + X^T X, Do = -(Y Y^T + Y^T Y) (may be null), lam_p [k][nv], lam_h [k][no]
-// (squared singular values, descending).
+// (squared singular values, descending). work: nto_work(k, nv, no) doubles; one_launch: the
+// eigenvalues of the blocks of order m with nto_spectra(m) by launch_spectra, lost [2] its flags for
+// the two blocks (set: launch again without).
+bool nto_spectra(int m);
+size_t nto_work(int k, int nv, int no);
 hipError_t launch_nto(const double* Z, int64_t ldz, int k, const Geometry& g, const int* ptab,
                       double* X, double* Y, double* Gx, double* Gy, double* Dv, double* Do,
-                      double* lam_p, double* lam_h, hipStream_t s);
+                      double* lam_p, double* lam_h, double* work, int* lost, bool one_launch,
+                      hipStream_t s);
 // The same for k packed alpha-beta roots: X = nva x nvb and Y = noa x nob read in place from Z
 // (alpha index outer); Gx = X X^T [k][nva][nva], Gy = Y Y^T (destroyed); Dv [k][nva^2 + nvb^2]
 // = (X X^T, X^T X), Do [k][noa^2 + nob^2] = -(Y Y^T, Y^T Y) (may be null); lam_p [k][nva],
-// lam_h [k][noa] (eigenvalues of X X^T and Y Y^T, descending, clamped at zero). All <= 512.
+// lam_h [k][noa] (eigenvalues of X X^T and Y Y^T, descending, clamped at zero). All <= 512. work:
+// nto_work(k, nva, noa) doubles.
 hipError_t launch_nto_ab(const double* Z, int64_t ldz, int k, int nva, int nvb, int noa, int nob,
                          double* Gx, double* Gy, double* Dv, double* Do, double* lam_p,
-                         double* lam_h, hipStream_t s);
+                         double* lam_h, double* work, int* lost, bool one_launch, hipStream_t s);
 // The packed roots' triangular amplitude matrices X [k][nv][nv], Y [k][no][no] (zeros below).
 hipError_t launch_unpack_triangular(const double* Z, int64_t ldz, int k, const Geometry& g,
                                     const int* ptab, double* X, double* Y, hipStream_t s);

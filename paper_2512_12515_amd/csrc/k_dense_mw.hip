@@ -381,14 +381,20 @@ __device__ __forceinline__ int mw_sturm_below(const double* __restrict__ t2, int
   return cnt;
 }
 
-// The last two diagonal and the last off-diagonal entry (from S, if given), then the Gershgorin interval of T:
+constexpr __host__ __device__ size_t sturm_elems(int n) { return 2 * ((size_t)n + 15); }
+
+// Matrix blockIdx.x: the last two diagonal and the last off-diagonal entry (from S, if given), then the Gershgorin interval of T:
 // bnd[0] = lower, bnd[1] = upper, bnd[2] = a norm of T, and t2: T
-// scaled by bnd[3], a power of two, as mw_sturm_below takes it (one workgroup).
+// scaled by bnd[3], a power of two, as mw_sturm_below takes it.
 __global__ __launch_bounds__(1024) void k_mw_bounds(const double* __restrict__ S, int n,
                                                     double* __restrict__ d, double* __restrict__ e,
                                                     double* __restrict__ bnd,
                                                     double* __restrict__ t2) {
   __shared__ double red[16];
+  d += (size_t)blockIdx.x * n;
+  e += (size_t)blockIdx.x * n;
+  bnd += blockIdx.x * 4;
+  t2 += blockIdx.x * sturm_elems(n);
   if (S && threadIdx.x == 0) {
     if (n >= 2) {
       d[n - 2] = S[(int64_t)(n - 2) * n + n - 2];
@@ -427,10 +433,14 @@ __global__ __launch_bounds__(1024) void k_mw_bounds(const double* __restrict__ S
 // A wave runs until its brackets are done. A whole wave an eigenvalue (9 rounds instead of 13) as
 // long as their waves fit the chip together (n <= 4096). n = 1071: 0.32 ms, against 1.43 with 16
 // lanes and the ratios' divisions.
-template <int L>
+// DOWN: the eigenvalues of matrix blockIdx.y, descending and clamped at zero.
+template <int L, bool DOWN>
 __global__ __launch_bounds__(256) void k_mw_bisect(const double* __restrict__ t2, int n,
                                                    const double* __restrict__ bnd,
                                                    double* __restrict__ lam) {
+  t2 += blockIdx.y * sturm_elems(n);
+  bnd += blockIdx.y * 4;
+  lam += (size_t)blockIdx.y * n;
   const int gid = blockIdx.x * 256 + threadIdx.x;
   const int idx = gid / L, g = gid % L;
   const double tnorm = bnd[2], sc = bnd[3];
@@ -462,7 +472,8 @@ __global__ __launch_bounds__(256) void k_mw_bisect(const double* __restrict__ t2
       }
     }
   }
-  if (idx < n && g == 0) lam[idx] = 0.5 * (lo + hi);
+  const double mid = 0.5 * (lo + hi);
+  if (idx < n && g == 0) lam[DOWN ? n - 1 - idx : idx] = DOWN ? fmax(mid, 0.0) : mid;
 }
 
 // out[0] = sum over lambda > 0 of (mu2 + lambda) - Tr A, out[1] = -(sum over lambda < 0 of
@@ -995,6 +1006,25 @@ static hipError_t mw_reduce(const double* M, int n, int64_t nvv, double mu2, dou
 }
 
 
+size_t spectra_work(int n, int nmat) {
+  return nmat * (tridiag_exchange(n) + 2 * (size_t)n + sturm_elems(n) + 4);
+}
+
+hipError_t launch_spectra(double* S, int n, int nmat, double* lam, double* work, int* lost,
+                          hipStream_t s) {
+  double* X = work;
+  double* d = X + nmat * tridiag_exchange(n);
+  double* e = d + (size_t)nmat * n;
+  double* t2 = e + (size_t)nmat * n;
+  double* bnd = t2 + nmat * sturm_elems(n);
+  const hipError_t rc = launch_tridiag(S, n, nmat, X, d, e, nullptr, lost, s);
+  if (rc != hipSuccess) return rc;
+  hipLaunchKernelGGL(k_mw_bounds, dim3(nmat), dim3(1024), 0, s, (const double*)nullptr, n, d, e, bnd, t2);
+  hipLaunchKernelGGL((k_mw_bisect<64, true>), dim3((unsigned)((n + 3) / 4), nmat), dim3(256), 0, s, t2,
+                     n, bnd, lam);
+  return hipGetLastError();
+}
+
 hipError_t launch_pencil_energy_mw(const double* M, int n, int64_t nvv, double mu2, double* out,
                                    double* work, int* info, bool one_launch, hipStream_t s) {
   if (n < 32 || n > DENSE_ENERGY_MAX) return hipErrorInvalidValue;
@@ -1012,10 +1042,10 @@ hipError_t launch_pencil_energy_mw(const double* M, int n, int64_t nvv, double m
   const hipError_t rc = mw_reduce(M, n, nvv, mu2, K, S, X, v2, p, d, e, bsc, nullptr, flag, info + 1, s);
   if (rc != hipSuccess) return rc;
   if (n <= 4096)
-    hipLaunchKernelGGL(k_mw_bisect<64>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, v2, n,
+    hipLaunchKernelGGL((k_mw_bisect<64, false>), dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, v2, n,
                        bsc + 2, lam);
   else
-    hipLaunchKernelGGL(k_mw_bisect<16>, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, v2, n,
+    hipLaunchKernelGGL((k_mw_bisect<16, false>), dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, v2, n,
                        bsc + 2, lam);
   hipLaunchKernelGGL(k_mw_sums, dim3(1), dim3(1024), 0, s, M, n, nvv, mu2, lam, flag, out, info);
   return hipGetLastError();

@@ -1110,21 +1110,50 @@ __global__ void k_unpack_triangular(const double* __restrict__ Z, int64_t ldz, i
     Y[((int64_t)r * no + p) * no + q] = v;
 }
 
-// Per root (blockIdx.y): Gt = T^T T and D = sgn (T T^T + T^T T) for the m x m matrices T.
-__global__ void k_triangular_products(const double* __restrict__ T, int m, double sgn,
-                                      double* __restrict__ Gt, double* __restrict__ D) {
-  const int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x;
-  const int r = blockIdx.y;
-  if (e >= (int64_t)m * m) return;
-  const int i = (int)(e / m), j = (int)(e % m);
-  const double* A = T + (int64_t)r * m * m;
-  double tt = 0.0, ttt = 0.0;  // (T T^T)_ij, (T^T T)_ij
-  for (int c = 0; c < m; ++c) {
-    tt += A[i * m + c] * A[j * m + c];
-    ttt += A[c * m + i] * A[c * m + j];
+// Per root (blockIdx.y): Gt = T^T T and D = sgn (T T^T + T^T T) for the m x m matrices T, a 32 x 32
+// tile (I >= J, both triangles written) per workgroup through LDS, four elements a thread. With an
+// element a thread, all of both sums from memory, the row-wise one strided, it took 330 us for ten
+// 200 x 200 matrices; so 60.
+__global__ __launch_bounds__(256) void k_triangular_products(const double* __restrict__ Tall, int m,
+                                                             double sgn, double* __restrict__ Gt,
+                                                             double* __restrict__ D) {
+  constexpr int B = 32;
+  __shared__ double ri[B][B + 1], rj[B][B + 1], ci[B][B + 1], cj[B][B + 1];
+  int I = 0, J = blockIdx.x;
+  while (J > I) J -= ++I;
+  const size_t off = (size_t)blockIdx.y * m * m;
+  const double* T = Tall + off;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  double tt[4] = {0.0, 0.0, 0.0, 0.0}, ttt[4] = {0.0, 0.0, 0.0, 0.0};  // (T T^T)_ij, (T^T T)_ij
+  for (int c0 = 0; c0 < m; c0 += B) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int y = ty + 8 * q, c = c0 + tx, i = I * B + y, j = J * B + y, r = c0 + y;
+      ri[y][tx] = i < m && c < m ? T[(size_t)i * m + c] : 0.0;
+      rj[y][tx] = j < m && c < m ? T[(size_t)j * m + c] : 0.0;
+      ci[y][tx] = r < m && I * B + tx < m ? T[(size_t)r * m + I * B + tx] : 0.0;
+      cj[y][tx] = r < m && J * B + tx < m ? T[(size_t)r * m + J * B + tx] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int c = 0; c < B; ++c) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        tt[q] += ri[ty + 8 * q][c] * rj[tx][c];
+        ttt[q] += ci[c][ty + 8 * q] * cj[c][tx];
+      }
+    }
   }
-  Gt[(int64_t)r * m * m + e] = ttt;
-  if (D) D[(int64_t)r * m * m + e] = sgn * (tt + ttt);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = I * B + ty + 8 * q, j = J * B + tx;
+    if (i < m && j < m) {
+      const size_t ij = off + (size_t)i * m + j, ji = off + (size_t)j * m + i;
+      Gt[ij] = Gt[ji] = ttt[q];
+      if (D) D[ij] = D[ji] = sgn * (tt[q] + ttt[q]);
+    }
+  }
 }
 
 // G = A^T A of k matrices A (rows x cols, row-major, astride doubles apart): G [k][cols][cols],
@@ -1648,9 +1677,25 @@ hipError_t launch_svd_vectors(const double* A, int64_t astride, int rows, int co
   return hipGetLastError();
 }
 
+// Eigenvalues of the k Gram matrices G (m x m), descending, on several workgroups each wherever the
+// one-launch reduction takes the order (from 3 on): ten matrices of order 16 / 200 by one workgroup
+// each take 161 us / 2.85 ms, so 70 us / 0.66 ms.
+bool nto_spectra(int m) { return tridiag_fits(m); }
+
+size_t nto_work(int k, int nv, int no) {
+  return std::max(nto_spectra(nv) ? spectra_work(nv, k) : 0, nto_spectra(no) ? spectra_work(no, k) : 0);
+}
+
+static hipError_t gram_eigenvalues(double* G, int m, int k, double* lam, double* work, int* lost,
+                                   bool one_launch, hipStream_t s) {
+  if (one_launch && nto_spectra(m)) return launch_spectra(G, m, k, lam, work, lost, s);
+  hipLaunchKernelGGL(k_gram_eigenvalues, dim3(k), dim3(WG), 0, s, G, m, lam);
+  return hipGetLastError();
+}
+
 hipError_t launch_nto_ab(const double* Z, int64_t ldz, int k, int nva, int nvb, int noa, int nob,
                          double* Gx, double* Gy, double* Dv, double* Do, double* lam_p,
-                         double* lam_h, hipStream_t s) {
+                         double* lam_h, double* work, int* lost, bool one_launch, hipStream_t s) {
   if (k < 1 || nva > JMAX || nvb > JMAX || noa > JMAX || nob > JMAX) return hipErrorInvalidValue;
   const int64_t nvv = (int64_t)nva * nvb;
   const int64_t ev = (int64_t)nva * nva + (int64_t)nvb * nvb;
@@ -1658,22 +1703,21 @@ hipError_t launch_nto_ab(const double* Z, int64_t ldz, int k, int nva, int nvb, 
                      ldz, (int64_t)0, nva, nvb, 1.0, Gx, Dv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gram_eigenvalues, dim3(k), dim3(WG), 0, s, Gx, nva, lam_p);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = gram_eigenvalues(Gx, nva, k, lam_p, work, lost, one_launch, s)) != hipSuccess) return e;
   if (noa > 0) {
     const int64_t eo = (int64_t)noa * noa + (int64_t)nob * nob;
     hipLaunchKernelGGL(k_rect_products, dim3((unsigned)((eo + NT - 1) / NT), k), dim3(NT), 0, s,
                        Z, ldz, nvv, noa, nob, -1.0, Gy, Do);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gram_eigenvalues, dim3(k), dim3(WG), 0, s, Gy, noa, lam_h);
-    e = hipGetLastError();
+    e = gram_eigenvalues(Gy, noa, k, lam_h, work, lost + 1, one_launch, s);
   }
   return e;
 }
 
 hipError_t launch_nto(const double* Z, int64_t ldz, int k, const Geometry& g, const int* ptab,
                       double* X, double* Y, double* Gx, double* Gy, double* Dv, double* Do,
-                      double* lam_p, double* lam_h, hipStream_t s) {
+                      double* lam_p, double* lam_h, double* work, int* lost, bool one_launch,
+                      hipStream_t s) {
   if (k < 1 || g.nv > JMAX || g.no > JMAX) return hipErrorInvalidValue;
   const size_t xv = (size_t)k * g.nv * g.nv, yo = (size_t)k * g.no * g.no;
   hipError_t e = launch_fill(X, xv, 0.0, s);
@@ -1682,18 +1726,16 @@ hipError_t launch_nto(const double* Z, int64_t ldz, int k, const Geometry& g, co
   hipLaunchKernelGGL(k_unpack_triangular, dim3((unsigned)((g.n + NT - 1) / NT), k), dim3(NT), 0, s,
                      Z, ldz, g.n, g.nvv, g.nv, g.no, ptab, X, Y);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int64_t mv = (int64_t)g.nv * g.nv, mo = (int64_t)g.no * g.no;
-  hipLaunchKernelGGL(k_triangular_products, dim3((unsigned)((mv + NT - 1) / NT), k), dim3(NT), 0, s,
-                     X, g.nv, 1.0, Gx, Dv);
+  const int tv = (g.nv + 31) / 32, to = (g.no + 31) / 32;
+  hipLaunchKernelGGL(k_triangular_products, dim3(tv * (tv + 1) / 2, k), dim3(256), 0, s, X, g.nv, 1.0,
+                     Gx, Dv);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gram_eigenvalues, dim3(k), dim3(WG), 0, s, Gx, g.nv, lam_p);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = gram_eigenvalues(Gx, g.nv, k, lam_p, work, lost, one_launch, s)) != hipSuccess) return e;
   if (g.no > 0) {
-    hipLaunchKernelGGL(k_triangular_products, dim3((unsigned)((mo + NT - 1) / NT), k), dim3(NT), 0,
-                       s, Y, g.no, -1.0, Gy, Do);
+    hipLaunchKernelGGL(k_triangular_products, dim3(to * (to + 1) / 2, k), dim3(256), 0, s, Y, g.no,
+                       -1.0, Gy, Do);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gram_eigenvalues, dim3(k), dim3(WG), 0, s, Gy, g.no, lam_h);
-    e = hipGetLastError();
+    e = gram_eigenvalues(Gy, g.no, k, lam_h, work, lost + 1, one_launch, s);
   }
   return e;
 }

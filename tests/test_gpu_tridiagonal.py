@@ -4,8 +4,12 @@ Sturm counts, inverse iteration, back-transformation) at the orders where its ke
 the reduction), 1087 / 1089 (the reduction in one launch or two launches a step), 2046 / 2052 (the
 vectors in LDS and registers or in memory), against the oracle's whole spectrum.
 
+The NTO weights of random vectors, which take the same reduction for several matrices at once, at
+block orders 2 / 3 (one workgroup or several), around the product kernel's tiles of 32, 256 / 257,
+and with more matrices than one launch holds (64 of order 130: 5 workgroups each).
+
 Tolerances as in the other tests of these calls: roots and residuals 1e-9, W-norms 1e-10, energies
-1e-10 Ha up to n = 513 and 1e-9 Ha above.
+1e-10 Ha up to n = 513 and 1e-9 Ha above; NTO weights and densities 1e-12 of the largest.
 """
 import sys
 
@@ -46,3 +50,19 @@ def test_dense_chain_at_the_kernels_edges(nocc, nvir, n):
         e = ctx.correlation_energy()
     assert abs(e["ec_pp"] - ec) <= (1e-10 if n <= 513 else 1e-9)
     assert abs(e["ec_hh"] - ec) <= (1e-10 if n <= 513 else 1e-9)
+
+
+@pytest.mark.parametrize("nocc,nvir,k", [(2, 3, 3), (3, 33, 5), (31, 32, 2), (33, 256, 2),
+                                         (1, 257, 3), (4, 130, 64)])
+def test_nto_weights_at_the_kernels_edges(nocc, nvir, k):
+    print("nto", nocc, nvir, k, flush=True)
+    sys.stdout.flush()
+    eps, L = gen.orbital_energies(62, nocc, nvir), gen.lpq_full(62, nocc + nvir, 8)
+    with P.PpRPA(eps, L, nocc, mult="singlet") as ctx:
+        Z = gen.random_vectors(63, k, ctx.n)
+        res = ctx.nto(Z)
+    for j, z in enumerate(Z):
+        lp, lh, _ = O.nto(z, nvir, nocc, "singlet")
+        Dv, Do = O.density_2e(z, nvir, nocc, "singlet")
+        for got, ref in ((res["lam_p"], lp), (res["lam_h"], lh), (res["d_vv"], Dv), (res["d_oo"], Do)):
+            assert np.max(np.abs(got[j] - ref)) <= 1e-12 * max(np.abs(ref).max(), 1e-300)
