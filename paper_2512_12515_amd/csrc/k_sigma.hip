@@ -114,7 +114,7 @@ __global__ void k_stage_L_bf16(const double* __restrict__ Lin, int nin, int p0,
   const unsigned short m = bf16_rne((float)r1);
   const double r2 = r1 - (double)bf16_to_f(m);
   const unsigned short l = bf16_rne((float)r2);
-  const size_t o = ((size_t)(p0 + P) * nmop + r) * nmop + c;
+  const size_t o = (size_t)(p0 + P) * nmop * nmop + bf16_at(r, c, nmop);
   Lout[o] = h;
   Lout[o + plane] = m;
   Lout[o + 2 * plane] = l;
@@ -178,15 +178,15 @@ __global__ void k_unpack_bf16(const double* __restrict__ z, int64_t n, int64_t n
   int d, c, off;
   double v;
   if (e < nvb) {
-    d = (int)(e / nvp);
-    c = (int)(e % nvp);
+    c = (int)(e / nvp);
+    d = (int)(e % nvp);
     off = 0;
     v = unpacked_value(z + (int64_t)kv * n, nv, mult, c, d);
   } else {
     e -= nvb;
     if (e >= (int64_t)nop * nop) return;
-    d = (int)(e / nop);
-    c = (int)(e % nop);
+    c = (int)(e / nop);
+    d = (int)(e % nop);
     off = nvp;
     v = unpacked_value(z + (int64_t)kv * n + nvv, no, mult, c, d);
   }
@@ -195,7 +195,7 @@ __global__ void k_unpack_bf16(const double* __restrict__ z, int64_t n, int64_t n
   const unsigned short m = bf16_rne((float)r1);
   const double r2 = r1 - (double)bf16_to_f(m);
   const unsigned short l = bf16_rne((float)r2);
-  const size_t o = ((size_t)kv * nmop + off + c) * nmop + off + d;  // U itself, row c
+  const size_t o = (size_t)kv * nmop * nmop + bf16_at(off + c, off + d, nmop);  // U itself
   ZT[o] = h;
   ZT[o + zplane] = m;
   ZT[o + 2 * zplane] = l;

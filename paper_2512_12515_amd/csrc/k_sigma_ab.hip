@@ -318,7 +318,7 @@ __global__ void k_unpack_ab_bf16(const double* __restrict__ z, int64_t n, int64_
   const unsigned short m = bf16_rne((float)r1);
   const double r2 = r1 - (double)bf16_to_f(m);
   const unsigned short l = bf16_rne((float)r2);
-  const size_t o = (size_t)kv * zstride + (size_t)c * nmopb + d;
+  const size_t o = (size_t)kv * zstride + bf16_at(c, d, nmopb);
   ZU[o] = h;
   ZU[o + zplane] = m;
   ZU[o + 2 * zplane] = l;
@@ -414,9 +414,9 @@ __global__ __launch_bounds__(256) void k_sandwich_ab_bf16(const u16* __restrict_
           __syncthreads();
 #pragma unroll
           for (int p = 0; p < NPL; ++p) {
-            dma_tile32(Z + p * zplane + (int64_t)(clo * TILE) * a.nmopb + dt * TILE, a.nmopb,
+            dma_tile32(Z + p * zplane + (int64_t)(clo * TILE) * a.nmopb + bf16_cols(dt), a.nmopb,
                        (chi - clo) * TILE, sU + p * Cfg::US, w, lane);
-            dma_tile32(Lbp + p * plane_b + (int64_t)col0 * a.nmopb + dt * TILE, a.nmopb, ncol,
+            dma_tile32(Lbp + p * plane_b + (int64_t)col0 * a.nmopb + bf16_cols(dt), a.nmopb, ncol,
                        sL + p * Cfg::LS, w, lane);
           }
           __builtin_amdgcn_s_waitcnt(0);
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(256) void k_sandwich_ab_bf16(const u16* __restrict_
 #pragma unroll
               for (int p = 0; p < NPL; ++p)
                 dma_tile32(Lap + p * plane_a + (int64_t)(row0 + rh0 * TILE) * a.nmopa +
-                               (cc0 + 2 * cb) * TILE,
+                               bf16_cols(cc0 + 2 * cb),
                            a.nmopa, nr * TILE, buf + p * Cfg::RS, w, lane);
               __builtin_amdgcn_s_waitcnt(0);
               __syncthreads();

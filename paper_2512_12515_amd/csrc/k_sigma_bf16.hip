@@ -150,9 +150,9 @@ __device__ __forceinline__ void sandwich_bf16_cols(const u16* __restrict__ L, si
           __syncthreads();
 #pragma unroll
           for (int p = 0; p < NPL; ++p) {
-            dma_tile32(Z + p * zplane + (int64_t)(g0 * TILE) * a.nmop + dt * TILE, a.nmop,
+            dma_tile32(Z + p * zplane + (int64_t)(g0 * TILE) * a.nmop + bf16_cols(dt), a.nmop,
                        (h1 - g0) * TILE, sU + p * Cfg::US, w, lane);
-            dma_tile32(Lp + p * plane + (int64_t)col0 * a.nmop + dt * TILE, a.nmop, ncol,
+            dma_tile32(Lp + p * plane + (int64_t)col0 * a.nmop + bf16_cols(dt), a.nmop, ncol,
                        sL + p * Cfg::LS, w, lane);
           }
           __builtin_amdgcn_s_waitcnt(0);
@@ -199,7 +199,7 @@ __device__ __forceinline__ void sandwich_bf16_cols(const u16* __restrict__ L, si
               __syncthreads();
 #pragma unroll
               for (int p = 0; p < NPL; ++p)
-                dma_tile32(Lp + p * plane + (int64_t)(row0 + rh0 * TILE) * a.nmop + (cc0 + i) * TILE,
+                dma_tile32(Lp + p * plane + (int64_t)(row0 + rh0 * TILE) * a.nmop + bf16_cols(cc0 + i),
                            a.nmop, nr * TILE, buf + p * Cfg::RS, w, lane);
               __builtin_amdgcn_s_waitcnt(0);
               __syncthreads();
@@ -308,9 +308,9 @@ __device__ __forceinline__ void sandwich_bf16_rows(const u16* __restrict__ L, si
           __syncthreads();
 #pragma unroll
           for (int p = 0; p < NPL; ++p) {
-            dma_tile32(Z + p * zplane + (int64_t)(g0 * TILE) * a.nmop + dt * TILE, a.nmop,
+            dma_tile32(Z + p * zplane + (int64_t)(g0 * TILE) * a.nmop + bf16_cols(dt), a.nmop,
                        (h1 - g0) * TILE, sU + p * Cfg::US, w, lane);
-            dma_tile32(Lp + p * plane + (int64_t)col0 * a.nmop + dt * TILE, a.nmop, ncol,
+            dma_tile32(Lp + p * plane + (int64_t)col0 * a.nmop + bf16_cols(dt), a.nmop, ncol,
                        sL + p * Cfg::LS, w, lane);
           }
           __builtin_amdgcn_s_waitcnt(0);
@@ -375,7 +375,7 @@ __device__ __forceinline__ void sandwich_bf16_rows(const u16* __restrict__ L, si
 #pragma unroll
               for (int p = 0; p < NPL; ++p)
                 dma_tile32(Lp + p * plane + (int64_t)(row0 + rh0 * TILE) * a.nmop +
-                               (cc0 + 2 * cb) * TILE,
+                               bf16_cols(cc0 + 2 * cb),
                            a.nmop, nr * TILE, buf + p * Cfg::RS, w, lane);
               __builtin_amdgcn_s_waitcnt(0);
               __syncthreads();
@@ -542,17 +542,16 @@ __device__ __forceinline__ void sandwich_bf16_cols_pipe(const u16* __restrict__ 
       c_range(s.pos + 1, s.cc0, s.cc1, a.nvt, &h0, &h1);
 #pragma unroll
       for (int p = 0; p < NPL; ++p) {
-        dma_tile32<QNW>(Z + p * zplane + (int64_t)(g0 * TILE) * a.nmop + s.pos * TILE, a.nmop,
+        dma_tile32<QNW>(Z + p * zplane + (int64_t)(g0 * TILE) * a.nmop + bf16_cols(s.pos), a.nmop,
                         (h1 - g0) * TILE, b + p * Cfg::US, w, lane);
-        dma_tile32<QNW>(Lp + p * plane + (int64_t)col0 * a.nmop + s.pos * TILE, a.nmop, ncol,
+        dma_tile32<QNW>(Lp + p * plane + (int64_t)col0 * a.nmop + bf16_cols(s.pos), a.nmop, ncol,
                         b + NPL * Cfg::US + p * Cfg::LS, w, lane);
       }
     } else {
       const int nr = min(RH, s.nrt - s.hh * RH);
 #pragma unroll
       for (int p = 0; p < NPL; ++p)
-        dma_tile32<QNW>(Lp + p * plane + (int64_t)(row0 + s.hh * RH * TILE) * a.nmop +
-                            s.pos * TILE,
+        dma_tile32<QNW>(Lp + p * plane + (int64_t)(row0 + s.hh * RH * TILE) * a.nmop + bf16_cols(s.pos),
                         a.nmop, nr * TILE, b + p * Cfg::RS, w, lane);
     }
   };

@@ -27,6 +27,18 @@ __device__ __forceinline__ float bf16_to_f(unsigned short h) {
   return __uint_as_float(((unsigned)h) << 16);
 }
 
+// A plane of an n x ld matrix is stored as tiles of 16 rows x 32 columns, each 1 KiB contiguous (row
+// tiles in order, the tiles of one in the order of their columns; n a multiple of 16, ld of 32), so
+// that a wave's load of a tile is 8 whole cache lines. Row-major, a tile was 16 half lines, each a
+// request of its own, and the single-buffered kernels waited for those: 40/400/1540 with 12 vectors, six
+// products 39.5 -> 33.2 ms, three 23.8 -> 20.1; 50/500/1800 three 73.7 -> 65.8 (six, double-buffered:
+// 116.3 as before).
+__device__ __forceinline__ size_t bf16_at(int r, int c, int ld) {
+  return (size_t)(r & ~15) * ld + (c >> 5) * 512 + (r & 15) * 32 + (c & 31);
+}
+// Offset of the tile of tile row 0 that starts at (16-wide) tile column t, t even.
+__device__ __forceinline__ int bf16_cols(int t) { return t * 256; }
+
 // LDS layout of a staged rows x 32 BF16 tile: each 64-byte row holds four 16-byte chunks, stored
 // at position kc ^ swz(row) so that the lanes one LDS cycle serves (rows r .. r+7 or r .. r+15 of
 // one chunk column) fall in distinct banks. The direct global->LDS loads write each wave's 1 KiB
@@ -38,8 +50,8 @@ __device__ __forceinline__ void dma_tile32(const u16* __restrict__ src, int64_t 
                                            u16* dst, int w, int lane) {
   const int nchunk = rows / 16;  // 16 rows x 64 bytes per wave load
   for (int j = w; j < nchunk; j += NWV) {
-    const int row = j * 16 + (lane >> 2), pos = lane & 3;
-    __builtin_amdgcn_global_load_lds((const void*)(src + row * ld + 8 * (pos ^ swz(row))),
+    const int row = lane >> 2, pos = lane & 3;
+    __builtin_amdgcn_global_load_lds((const void*)(src + j * 16 * ld + row * 32 + 8 * (pos ^ swz(row))),
                                      (lds_ptr_t)(dst + j * 512), 16, 0, 0);
   }
 }
