@@ -648,6 +648,9 @@ hipError_t launch_sigma(const Geometry& g, Store st, const SigmaPlan& plan, cons
                         hipStream_t s) {
   const MmGeometry mg = mm_geometry(g);
   const MmPlan m = mm_plan(st, mg, la.k, la.nsplit * la.k);
+  if (m.nslot > 0 && st == Store::BF16)
+    return launch_sigma_bf16_mm(mg, m, la.nprod, la.L, la.plane, la.ZT, la.zplane, la.Sp, la.ws_slots,
+                                la.k, s);
   if (m.nslot > 0)
     return launch_sigma_mm(st, mg, m, la.L, la.L, la.ZT, la.Sp, la.ws_slots, la.k, s);
   switch (plan.variant) {

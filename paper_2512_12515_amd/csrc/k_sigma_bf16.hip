@@ -32,6 +32,9 @@
 // wider panel halves the staged U and L^P rows per product, which is what bounds these kernels
 // at that size (a timing probe of an 8-wave form on 4-tile panels ran 1.44x faster with its
 // loads removed; double-buffering alone did not help it).
+// Blocks of 160 column tiles and more at 13 or more virtual tiles go to the two-product form
+// (k_sigma_bf16_mm.hip), which shares the staged rows over more products; these kernels are for fewer
+// vectors, smaller blocks and few aux indices.
 #include "sigma_common.h"
 #include "sigma_bf16.h"
 

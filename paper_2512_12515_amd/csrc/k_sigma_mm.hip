@@ -466,9 +466,11 @@ MmGeometry mm_geometry(const AbGeometry& g) {
 static SigmaSums sums_of(const MmGeometry& g, Store st, int k, int nsplit) {
   const int64_t zz = (int64_t)g.ncta * g.nctb * TILE * TILE, ld = g.nctb * TILE;
   const MmPlan m = mm_plan(st, g, k, nsplit * k);
-  if (m.nslot == 0)
-    return {st == Store::F64 ? Store::F64 : Store::F32, nsplit, zz, k * zz,
-            nsplit, g.nvta * TILE * ld + g.nvtb * TILE, ld, zz, k * zz};
+  if (m.nslot == 0 || st == Store::BF16) {
+    const int ns = m.nslot ? m.nslot : nsplit;
+    return {st == Store::F64 ? Store::F64 : Store::F32, ns, zz, k * zz,
+            ns, g.nvta * TILE * ld + g.nvtb * TILE, ld, zz, k * zz};
+  }
   const int64_t ldo = (g.nctb - g.nvtb) * TILE, zo = (g.ncta - g.nvta) * TILE * ldo;
   return {Store::F64, m.nslot, zz, k * zz, m.nslot * m.ro, m.nslot * k * zz, ldo, zo, k * zo};
 }
@@ -482,38 +484,42 @@ SigmaSums sigma_sums(const AbGeometry& g, Store st, int k, int nsplit) {
 // Workspace of the (FP64) sums of k vectors, in matrices of the sigma precision.
 static int64_t sum_slots(Store st, const MmGeometry& g, int k, int nslot, int ro) {
   const int64_t zz = (int64_t)g.ncta * g.nctb, zo = (int64_t)(g.ncta - g.nvta) * (g.nctb - g.nvtb);
+  if (st == Store::BF16) return (int64_t)nslot * k;  // FP32, both blocks in one matrix
   const int64_t one = (int64_t)nslot * k + ((int64_t)nslot * ro * k * zo + zz - 1) / zz;
   return st == Store::F64 ? one : 2 * one;
 }
 
 MmPlan mm_plan(Store st, const MmGeometry& g, int k, int slots) {
   MmPlan m;
-  if (st == Store::BF16 || g.naux < MM_MIN_NAUX || (g.ncta > g.nvta) != (g.nctb > g.nvtb) ||
+  const bool bf = st == Store::BF16;
+  if ((bf && (!g.tri || g.nvta < BF_MIN_NVT)) || g.naux < MM_MIN_NAUX || (g.ncta > g.nvta) != (g.nctb > g.nvtb) ||
       g.nvta == 0 || g.nvtb == 0)
     return m;
-  const int tiles = k * g.nvtb, wgs = 512;  // two workgroups a CU
-  if (tiles < (st == Store::F64 ? MM_MIN_TILES_F64 : MM_MIN_TILES_F32)) return m;
+  const int tiles = k * g.nvtb, wgs = bf ? 256 : 512;  // workgroups the chip holds
+  if (tiles < (st == Store::F64 ? MM_MIN_TILES_F64 : (bf ? BF_MIN_TILES : MM_MIN_TILES_F32))) return m;
   const int ota = g.ncta - g.nvta, otb = g.nctb - g.nvtb;
-  m.npv = (g.nvta + MT - 1) / MT;
-  m.npo = (ota + MT - 1) / MT;
+  if (bf && g.nvta < BF_MIN_FILL * ((g.nvta + 7) / 8 * 8)) return m;
+  const int mt = bf ? BF_MT : MT;
+  m.npv = (g.nvta + mt - 1) / mt;
+  m.npo = (ota + mt - 1) / mt;
   m.items2v = m.npv * ((tiles + MM_BT - 1) / MM_BT);
   m.items2 = m.items2v + m.npo * ((k * otb + MM_BT - 1) / MM_BT);
   // 32-bit lane offsets
-  if ((uint64_t)g.ncta * g.nctb * TILE * TILE * k * 8 * 3 >= (uint64_t(1) << 32)) return m;
+  if (!bf && (uint64_t)g.ncta * g.nctb * TILE * TILE * k * 8 * 3 >= (uint64_t(1) << 32)) return m;
   // phase 2 units fill whole rounds of the chip's workgroups as well as they can: the fewest slots
   // within 2 % of the best fill by the virtual block's units
   auto fill = [&](int ns) {
     const int units = m.items2v * ns, rounds = (units + wgs - 1) / wgs;
     return units / (double)(rounds * wgs);
   };
-  auto ro_of = [&](int ns) { return std::min(MM_RO, g.naux / ns); };
+  auto ro_of = [&](int ns) { return bf ? 1 : std::min(MM_RO, g.naux / ns); };
   // (the smallest workspace holds the sums and two buffers of four aux indices a slot, or of one)
   int most = 0;
   double best = 0;
   for (int pcs : {4, 2, 1}) {
     best = 0;
     for (int ns = 1; ns <= std::min(128, g.naux); ++ns)
-      if (sum_slots(st, g, k, ns, ro_of(ns)) + 2 * (int64_t)pcs * ns * k <= slots) {
+      if (sum_slots(st, g, k, ns, ro_of(ns)) + (bf ? 3 : 2) * (int64_t)pcs * ns * k <= slots) {
         most = ns;
         best = std::max(best, fill(ns));
       }

@@ -9,6 +9,7 @@ namespace pprpa {
 
 constexpr int MM_MT = 8;      // row tiles per panel
 constexpr int MM_BT = 8;      // column tiles per unit
+constexpr int BF_MT = 16;     // row tiles per panel of the BF16 form
 constexpr int MM_RO = 8;      // most slots of the occupied block per slot of the virtual one
 // Fewest column tiles of a block of vectors (k x virtual tiles) from which this form runs. us, the
 // one-kernel form -> this one: FP64 5/20/100 8 vectors (16 tiles) 66 -> 57, 13/117/457 1 vector (8)
@@ -16,6 +17,15 @@ constexpr int MM_RO = 8;      // most slots of the occupied block per slot of th
 // 8/80/300 4 vectors (20) 143 -> 98.
 constexpr int MM_MIN_TILES_F64 = 16;
 constexpr int MM_MIN_TILES_F32 = 18;
+// BF16: fewest column tiles and virtual tiles, and the least share of their rows of four pairs that
+// the virtual tiles fill. us, the one-kernel form -> this one, six / three products: 20/200/700 20 vectors
+// (280 tiles) 4543 -> 4126 / 3060 -> 2737, 10 (140) 2302 -> 2361 / 1586 -> 1438; 40/400/1540 12 (312,
+// 13 pairs in 4 rows) 33.2e3 -> 29.9e3 / 20.1e3 -> 16.5e3, 2 (52) 5702 -> 5547 / 3426
+// -> 3658; 50/500/1800 20 (640) 116e3 -> 82e3 / 65.8e3 -> 46.3e3; 13/117/457 20 (8 virtual tiles) 814 ->
+// 1092 / 636 -> 722.
+constexpr int BF_MIN_TILES = 160;
+constexpr int BF_MIN_NVT = 13;
+constexpr double BF_MIN_FILL = 0.8;
 // Fewest aux indices: below, the one-kernel form has a split for every aux index whatever the block
 // width, and a vector's sigma does not depend on the block around it; that stays so.
 constexpr int MM_MIN_NAUX = 96;
@@ -44,6 +54,20 @@ __host__ __device__ inline int mm_cut(int lo, int hi, int n, int i) {
   return lo + (int)((int64_t)(hi - lo) * i / n);
 }
 
+// First row tile of panel i of n of bt tiles, BF16: even shares of the pairs of tiles, or of their rows
+// of four (a pair for each of four waves), whose last one is as it comes.
+__host__ __device__ inline int bf_cut(int bt, int n, int i, bool even) {
+  const int cut = even ? bt / 2 * i / n * 2 : (bt + 7) / 8 * i / n * 8;
+  return cut < bt ? cut : bt;
+}
+// Even shares as long as they make no more rows (26 tiles as 14 + 12 rather than 16 + 10: 40/400/1540
+// 5 % faster; but 24 as 16 + 8, 3 rows).
+inline bool bf_even(int bt, int n) {
+  int rows = 0;
+  for (int i = 0; i < n; ++i) rows += (bf_cut(bt, n, i + 1, true) - bf_cut(bt, n, i, true) + 7) / 8;
+  return rows == (bt + 7) / 8;
+}
+
 struct MmParams {
   int nvta, ncta, nvtb, nctb, nmopa, nmopb, k, tri;
   int npv, npo, items2v, items2, nslot, ro, naux;
@@ -68,5 +92,9 @@ MmPlan mm_plan(Store st, const MmGeometry& g, int k, int slots);
 hipError_t launch_sigma_mm(Store st, const MmGeometry& g, const MmPlan& m, const void* La,
                            const void* Lb, const void* UT, void* ws, int64_t ws_slots, int k,
                            hipStream_t s);
+// The same for BF16 planes of L (plane elements apart) and U (row-major, zplane apart), restricted.
+hipError_t launch_sigma_bf16_mm(const MmGeometry& g, const MmPlan& m, int nprod, const void* L,
+                                size_t plane, const void* U, size_t zplane, void* ws,
+                                int64_t ws_slots, int k, hipStream_t s);
 
 }  // namespace pprpa
