@@ -513,21 +513,26 @@ MmPlan mm_plan(Store st, const MmGeometry& g, int k, int slots) {
     return units / (double)(rounds * wgs);
   };
   auto ro_of = [&](int ns) { return bf ? 1 : std::min(MM_RO, g.naux / ns); };
-  // (the smallest workspace holds the sums and two buffers of four aux indices a slot, or of one)
-  int most = 0;
+  // (the smallest workspace holds the sums and two buffers of four aux indices a slot, or of one: each
+  // number of slots on its own, as fewer slots may take more sums of the occupied block)
+  int most = 0, parts = 4;
+  auto fits = [&](int ns) {
+    return sum_slots(st, g, k, ns, ro_of(ns)) + (bf ? 3 : 2) * (int64_t)parts * ns * k <= slots;
+  };
   double best = 0;
-  for (int pcs : {4, 2, 1}) {
+  for (;; parts /= 2) {
+    most = 0;
     best = 0;
     for (int ns = 1; ns <= std::min(128, g.naux); ++ns)
-      if (sum_slots(st, g, k, ns, ro_of(ns)) + (bf ? 3 : 2) * (int64_t)pcs * ns * k <= slots) {
+      if (fits(ns)) {
         most = ns;
         best = std::max(best, fill(ns));
       }
-    if (m.items2v * most >= 0.9 * wgs) break;
+    if (parts == 1 || m.items2v * most >= 0.9 * wgs) break;
   }
   if (most == 0) return m;
   m.nslot = 1;
-  while (m.nslot < most && fill(m.nslot) < best - 0.02) ++m.nslot;
+  while (!fits(m.nslot) || fill(m.nslot) < best - 0.02) ++m.nslot;
   m.ro = ro_of(m.nslot);
   m.qslots = sum_slots(st, g, k, m.nslot, m.ro);
   return m;
@@ -564,6 +569,7 @@ static hipError_t run_mm(const MmGeometry& g, const MmPlan& m, const void* La, c
   // parts of T: all of it in one buffer, or as much as two hold
   const int len = (g.naux + m.nslot - 1) / m.nslot;  // longest slot
   const int64_t room = (ws_slots - m.qslots) / ((int64_t)k * m.nslot);
+  if (room < 2 && room < len) return hipErrorInvalidValue;
   if (room >= len)
     p.nparts = 1;
   else

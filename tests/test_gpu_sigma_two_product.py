@@ -72,3 +72,20 @@ def test_served_equals_standalone(prec):
         r = srv.wait(srv.submit(eps, L, nocc, 10, mult="triplet", prec=prec, tol=1e-5), timeout=120.0)
     assert r["status"] == P.binding.OK, r["message"]
     assert np.array_equal(r["omega"], own)
+
+
+@pytest.mark.parametrize("nocc,nvir,naux,nroot,prec", [(59, 30, 96, 24, "fp64"), (50, 20, 130, 16, "fp64"),
+                                                       (44, 49, 173, 14, "fp32")])
+def test_served_with_a_large_occupied_block(nocc, nvir, naux, nroot, prec):
+    """Occupied blocks as large as the virtual one, where fewer slots take more sums: the smallest
+    workspace has to hold the number of slots that is taken, not only a larger one."""
+    print("two-product sigma served, large occupied block", nocc, nvir, naux, nroot, prec, flush=True)
+    eps = gen.orbital_energies(9, nocc, nvir)
+    L = 0.7 * gen.lpq_full(9, nocc + nvir, naux)
+    with P.PpRPA(eps, L, nocc, mult="singlet", prec=prec) as ctx:
+        own = ctx.davidson(nroot, block=nroot, tol=1e-4)["omega"]
+    with P.Server(2 << 30, 2) as srv:
+        r = srv.wait(srv.submit(eps, L, nocc, nroot, mult="singlet", prec=prec, block=nroot, tol=1e-4),
+                     timeout=60.0)
+    assert r["status"] == P.binding.OK, r["message"]
+    assert np.array_equal(r["omega"], own)
