@@ -314,10 +314,11 @@ pprpa_status setup_runtime(pprpa_ctx* c, void* stream) {
 
 // Partial sums of a sigma launch: at least `slots` matrices of `bytes` each. A context that runs the
 // two-product form outside a slab takes up to MM_WORKSPACE bytes instead, so that its products need
-// fewer, longer launches; it does with the least when that much is not free.
-pprpa_status alloc_sums(pprpa_ctx* c, const MmGeometry& mg, size_t slots, size_t bytes) {
+// fewer, longer launches; it does with the least when that much is not free. A dense context (least),
+// built for the direct solve, does too: the larger allocation is a third of its build at 5/20/100.
+pprpa_status alloc_sums(pprpa_ctx* c, const MmGeometry& mg, size_t slots, size_t bytes, bool least) {
   c->sp_slots = (int64_t)slots;
-  if (!c->slab && mm_plan(c->st, mg, c->kcap, nsplit_for(c, c->kcap) * c->kcap).nslot > 0) {
+  if (!c->slab && !least && mm_plan(c->st, mg, c->kcap, nsplit_for(c, c->kcap) * c->kcap).nslot > 0) {
     const size_t more = std::min(slots + (size_t)mg.naux * c->kcap, MM_WORKSPACE / bytes);
     if (more > slots && dalloc(c, more * bytes, &c->Sp) == PPRPA_OK) {
       c->sp_slots = (int64_t)more;
@@ -467,7 +468,7 @@ pprpa_status build_impl(const pprpa_build_args* a, pprpa_ctx* c) {
   PPRPA_TRY(dalloc(c, c->zplane * esz * nplanes, &c->ZT));
   PPRPA_HIP(hipMemsetAsync(c->ZT, 0, c->zplane * esz * nplanes, c->stream));
   const size_t spsz = c->st == Store::F64 ? 8 : 4;
-  PPRPA_TRY(alloc_sums(c, mm_geometry(g), sp_max, zz * spsz));
+  PPRPA_TRY(alloc_sums(c, mm_geometry(g), sp_max, zz * spsz, a->dense != 0));
   PPRPA_TRY(dalloc(c, (size_t)c->kcap * g.n * sizeof(double), (void**)&c->zbuf));
   PPRPA_TRY(dalloc(c, (size_t)c->kcap * g.n * sizeof(double), (void**)&c->sbuf));
 
@@ -637,7 +638,7 @@ pprpa_status build_ab_impl(const pprpa_build_ab_args* a, pprpa_ctx* c) {
     for (int kk = 1; kk <= c->kcap; ++kk)
       sp_max = std::max(sp_max, (size_t)nsplit_for(c, kk) * kk);
     PPRPA_TRY(alloc_sums(c, mm_geometry(ag), sp_max,
-                         (size_t)ag.nmopa * ag.nmopb * (c->st == Store::F64 ? 8 : 4)));
+                         (size_t)ag.nmopa * ag.nmopb * (c->st == Store::F64 ? 8 : 4), false));
   } else {
     PPRPA_TRY(dalloc(c, (size_t)g.n * g.n * sizeof(double), (void**)&c->M));
     PPRPA_HIP(launch_dense_build_ab(La, Lb, naux, nmo, noa, nob, g.n, g.nvv, c->ptab, c->epair,
