@@ -1679,7 +1679,7 @@ hipError_t launch_svd_vectors(const double* A, int64_t astride, int rows, int co
 
 // Eigenvalues of the k Gram matrices G (m x m), descending, on several workgroups each wherever the
 // one-launch reduction takes the order (from 3 on): ten matrices of order 16 / 200 by one workgroup
-// each take 161 us / 2.85 ms, so 70 us / 0.66 ms.
+// each take 161 us / 2.85 ms, so 70 us / 0.65 ms.
 bool nto_spectra(int m) { return tridiag_fits(m); }
 
 size_t nto_work(int k, int nv, int no) {

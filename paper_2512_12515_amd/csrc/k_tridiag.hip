@@ -21,9 +21,9 @@
 // piece (1.3 us from store to all workgroups having read, 2 with p in row order), and a reader
 // polls until it differs.
 //
-// What bounds it: latency, 2.7 us a step at n = 225 and 4.3 at n = 1071 (the exchange 1.3 and 1.9,
+// What bounds it: latency, 2.4 us a step at n = 225 and 3.9 at n = 1071 (the exchange 1.3 and 1.9,
 // the rest three sums over a wave, three barriers, a square root and a reciprocal, one after the
-// other); as two launches a step 6.4 and 11.2. In all 0.61 ms and 4.64 ms, before 1.44 and 11.96.
+// other); as two launches a step 6.4 and 11.2. In all 0.54 ms and 4.12 ms, before 1.44 and 11.96.
 //
 // Every wait ends: a workgroup's stores of step k depend on its own earlier steps and on the other
 // workgroups' stores of steps before k only, the workgroups of a launch fit the chip at once (at
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void k_tridiag_clear(double* __restrict__ X, s
   if (blockIdx.x == 0 && threadIdx.x == 0) *abort_flag = 0;
 }
 
-// Matrix blockIdx.x / G of S [..][n][n] (both triangles), exchange buffer X [..][exchange(n, ..)];
+// Matrix blockIdx.x / G of S [..][n][n] (both triangles), exchange buffer X [..][ldx];
 // d, e [..][n]; keep (one matrix): reflection k's vector is left in row k of S right of the
 // diagonal, its beta in beta_keep[k].
 template <int CPL, int RPW>
@@ -295,17 +295,14 @@ struct Gate {
 constexpr int GATES = 64;
 Gate g_gate[GATES];
 
-// Workgroups per matrix, and the elements that the exchange of one reduction takes.
-template <int RPW> int groups(int n) { return (n + TW * RPW - 1) / (TW * RPW); }
-template <int RPW> size_t exchange(int n) {
-  return (size_t)n * groups<RPW>(n) * TW * RPW + (size_t)n * n / 2;
-}
+// Workgroups per matrix at rpw rows a wave.
+int groups(int n, int rpw) { return (n + TW * rpw - 1) / (TW * rpw); }
 
 template <int CPL, int RPW>
 hipError_t run(double* S, int n, int nmat, double* X, double* d, double* e, double* beta_keep,
                int* abort_flag, int cus, hipStream_t s) {
-  const int G = groups<RPW>(n);
-  const size_t ldx = exchange<RPW>(n);
+  const int G = groups(n, RPW);
+  const size_t ldx = tridiag_exchange(n);
   const int batch = cus / G;  // matrices per launch
   for (int m0 = 0; m0 < nmat; m0 += batch) {
     const int nb = nmat - m0 < batch ? nmat - m0 : batch;
@@ -314,6 +311,20 @@ hipError_t run(double* S, int n, int nmat, double* X, double* d, double* e, doub
                        X + m0 * ldx, ldx, d + off, e + off, beta_keep, abort_flag);
   }
   return hipGetLastError();
+}
+
+// Rows a wave: as few as let every matrix have its workgroups at once (a step's products and updates
+// are shorter, and more workgroups exchange as fast: 4 / 2 / 1 rows 616 / 559 / 543 us at n = 225,
+// 1.57 / 1.36 / 1.29 ms at 451, 5.15 / 4.64 / 4.12 at 1071), else the most. The bits are the same: a
+// row's product and the sums over columns do not depend on it.
+template <int CPL, int MOST>
+hipError_t run_rows(double* S, int n, int nmat, double* X, double* d, double* e, double* beta_keep,
+                    int* abort_flag, int cus, hipStream_t s) {
+  if ((int64_t)nmat * groups(n, 1) <= cus)
+    return run<CPL, 1>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
+  if (MOST == 2 || (int64_t)nmat * groups(n, 2) <= cus)
+    return run<CPL, 2>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
+  return run<CPL, MOST>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
 }
 
 }  // namespace
@@ -326,8 +337,9 @@ bool tridiag_fits(int n) {
   return cus >= 128;
 }
 
+// n steps' pieces of every workgroup's rows (whatever their split) and the rows.
 size_t tridiag_exchange(int n) {
-  return n <= 512 ? exchange<4>(n) : exchange<2>(n);
+  return (size_t)n * (n + 4 * TW - 1) + (size_t)n * n / 2;
 }
 
 hipError_t launch_tridiag(double* S, int n, int nmat, double* X, double* d, double* e,
@@ -346,9 +358,9 @@ hipError_t launch_tridiag(double* S, int n, int nmat, double* X, double* d, doub
   }
   const size_t total = nmat * tridiag_exchange(n), blocks = std::min<size_t>((total + 1023) / 1024, 2048);
   hipLaunchKernelGGL(k_tridiag_clear, dim3((unsigned)blocks), dim3(256), 0, s, X, total, abort_flag);
-  rc = n <= 256   ? run<4, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
-       : n <= 512 ? run<8, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
-                  : run<17, 2>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
+  rc = n <= 256   ? run_rows<4, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
+       : n <= 512 ? run_rows<8, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
+                  : run_rows<17, 2>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
   if (rc == hipSuccess) rc = hipEventRecord(gt.last, s);
   return rc;
 }
