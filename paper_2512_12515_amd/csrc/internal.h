@@ -241,7 +241,7 @@ hipError_t launch_direct_pencil_mw(const double* M, int m, int64_t nvv, double m
 // where tridiag_fits; X: exchange buffer of nmat tridiag_exchange(n) doubles. beta_keep (nmat = 1): the reflection
 // vectors stay in the rows of S right of the diagonal. *abort_flag: 0, or 1 when the workgroups
 // lost one another (the outputs are then not usable).
-constexpr int TRIDIAG_MAX = 1088;
+constexpr int TRIDIAG_MAX = 2048;
 bool tridiag_fits(int n);
 size_t tridiag_exchange(int n);
 hipError_t launch_tridiag(double* S, int n, int nmat, double* X, double* d, double* e,

@@ -23,7 +23,8 @@
 //
 // What bounds it: latency, 2.4 us a step at n = 225 and 3.9 at n = 1071 (the exchange 1.3 and 1.9,
 // the rest three sums over a wave, three barriers, a square root and a reciprocal, one after the
-// other); as two launches a step 6.4 and 11.2. In all 0.54 ms and 4.12 ms, before 1.44 and 11.96.
+// other); as two launches a step 6.4 and 11.2. In all 0.54 ms and 4.12 ms, before 1.44 and 11.96;
+// 6.2 us a step at n = 1989, the widest rows, before 16.8.
 //
 // Every wait ends: a workgroup's stores of step k depend on its own earlier steps and on the other
 // workgroups' stores of steps before k only, the workgroups of a launch fit the chip at once (at
@@ -251,18 +252,35 @@ __global__ __launch_bounds__(64 * TW, 2) void k_tridiag(double* __restrict__ Sal
     s2 = wave_total(s2);
     if (lane == 0) part[1][w] = s2;
     __syncthreads();
-    // 4. this wave's rows
-    double wv[CPL];
+    // 4. this wave's rows (wide rows: v again from LDS, its registers hold the row)
+    if constexpr (CPL > 20) {
 #pragma unroll
-    for (int j = 0; j < CPL; ++j) wv[j] = wS[64 * j + lane];
+      for (int i = 0; i < RPW; ++i) {
+        const int r = (i * TW + w) * G + g;
+        if (r > k && r < n) {
+          const double vr = r == k + 1 ? vfirst : xS[par ^ 1][r], wr = wS[r];
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-      const int r = (i * TW + w) * G + g;
-      if (r > k && r < n) {
-        const double vr = r == k + 1 ? vfirst : xS[par ^ 1][r], wr = wS[r];
+          for (int j = 0; j < CPL; ++j)
+            if (j >= j0) {
+              const int c = 64 * j + lane;
+              const double vc = c == k + 1 ? vfirst : xS[par ^ 1][c];
+              A[i][j] -= vr * wS[c] + wr * vc;
+            }
+        }
+      }
+    } else {
+      double wv[CPL];
 #pragma unroll
-        for (int j = 0; j < CPL; ++j)
-          if (j >= j0) A[i][j] -= vr * wv[j] + wr * v[j];
+      for (int j = 0; j < CPL; ++j) wv[j] = wS[64 * j + lane];
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) {
+        const int r = (i * TW + w) * G + g;
+        if (r > k && r < n) {
+          const double vr = r == k + 1 ? vfirst : xS[par ^ 1][r], wr = wS[r];
+#pragma unroll
+          for (int j = 0; j < CPL; ++j)
+            if (j >= j0) A[i][j] -= vr * wv[j] + wr * v[j];
+        }
       }
     }
     g0 = g1;
@@ -334,7 +352,7 @@ bool tridiag_fits(int n) {
   if (n < 3 || n > TRIDIAG_MAX || hipGetDevice(&dev) != hipSuccess || dev >= GATES ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return false;
-  return cus >= 128;
+  return groups(n, n <= 512 ? 4 : n <= 1088 ? 2 : 1) <= cus;
 }
 
 // n steps' pieces of every workgroup's rows (whatever their split) and the rows.
@@ -360,7 +378,8 @@ hipError_t launch_tridiag(double* S, int n, int nmat, double* X, double* d, doub
   hipLaunchKernelGGL(k_tridiag_clear, dim3((unsigned)blocks), dim3(256), 0, s, X, total, abort_flag);
   rc = n <= 256   ? run_rows<4, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
        : n <= 512 ? run_rows<8, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
-                  : run_rows<17, 2>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
+       : n <= 1088 ? run_rows<17, 2>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
+                   : run<32, 1>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
   if (rc == hipSuccess) rc = hipEventRecord(gt.last, s);
   return rc;
 }

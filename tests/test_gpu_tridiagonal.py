@@ -1,8 +1,9 @@
 """GPU: the dense pencil's whole chain (Cholesky, tridiagonal form in one launch, eigenvalues by
 Sturm counts, inverse iteration, back-transformation) at the orders where its kernels change:
 97 (the first order on many workgroups), 256 / 258 and 511 / 513 (columns a lane and rows a wave of
-the reduction), 1087 / 1089 (the reduction in one launch or two launches a step), 2046 / 2052 (the
-vectors in LDS and registers or in memory), against the oracle's whole spectrum.
+the reduction), 1087 / 1089 (its widest rows, v kept in registers or read again), 2046 / 2052 (the
+reduction in one launch or two launches a step, the vectors in LDS and registers or in memory), against
+the oracle's whole spectrum.
 
 The NTO weights of random vectors, which take the same reduction for several matrices at once, at
 block orders 2 / 3 (one workgroup or several), around the product kernel's tiles of 32, 256 / 257,
