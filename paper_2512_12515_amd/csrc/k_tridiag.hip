@@ -13,6 +13,9 @@
 //   3. w = p - (beta p^T v / 2) v, the updated row k + 1 and its norm, from which the next
 //      reflection: two sums over the workgroup, the same in every workgroup;
 //   4. each wave updates its rows.
+// A kept reflection goes back into its row of S, which every workgroup has read by then: its rows and
+// row 0 are read ahead of its piece of step 0, and the rows are stored after a step's pieces of all
+// workgroups (each has a row right of row 0: there are no more workgroups than rows) have arrived.
 // One exchange between the workgroups and three barriers a step. (With step 3 done whole by each
 // wave, one barrier, a step was 2.5 times as long: 17 columns a lane of the same work in 8 waves.)
 // The exchanged words are their own flags: the exchange buffer is filled with a bit pattern that no
@@ -149,14 +152,6 @@ __global__ __launch_bounds__(64 * TW, 2) void k_tridiag(double* __restrict__ Sal
     for (int j = 0; j < CPL; ++j)
       if (j == j0) v[j] = lane == ((k + 1) & 63) ? vfirst : v[j];
     if (lead) e[k] = alpha;
-    if (beta_keep && g == g0 && w == q0 % TW) {
-      if (lane == 0) beta_keep[k] = beta;
-#pragma unroll
-      for (int j = 0; j < CPL; ++j) {
-        const int c = 64 * j + lane;
-        if (c > k && c < n) S[(size_t)k * n + c] = v[j];
-      }
-    }
     // 1. products of this wave's rows, published with row k + 1
     double* const P = X;  // a piece of RPG per workgroup, then R[c - k - 1]
     double* const R = X + G * RPG;
@@ -281,6 +276,17 @@ __global__ __launch_bounds__(64 * TW, 2) void k_tridiag(double* __restrict__ Sal
           for (int j = 0; j < CPL; ++j)
             if (j >= j0) A[i][j] -= vr * wv[j] + wr * v[j];
         }
+      }
+    }
+    // The kept reflection into row k of S. Not before the step's exchange: every workgroup takes the
+    // first reflection from row 0 of S when it starts, which may be late, and has done so when its
+    // piece of step 0 is there. (Rows from 1 on are read by their own workgroup only.)
+    if (beta_keep && g == g0 && w == q0 % TW) {
+      if (lane == 0) beta_keep[k] = beta;
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) {
+        const int c = 64 * j + lane;
+        if (c > k && c < n) S[(size_t)k * n + c] = c == k + 1 ? vfirst : xS[par ^ 1][c];
       }
     }
     g0 = g1;
