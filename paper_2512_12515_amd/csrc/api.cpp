@@ -764,11 +764,11 @@ pprpa_status corr_energy_run(pprpa_ctx* c, double* work, pprpa_corr_energy* out)
   int* dinfo = (int*)(dout + 4);
   double* hp = c->pinned;
   const int* info = (const int*)(hp + 4);
-  for (int one = 1; one >= 0; --one) {
+  for (int polls : {c->tridiag_polls, -1}) {
     // one workgroup up to order 96, many above (the no-allocation entry point goes to 512)
     hipError_t le = n <= DENSE_ONE_WG_MAX ? launch_pencil_energy(c->M, (int)n, nvv, c->mu2, dout, work, dinfo, c->stream)
                              : launch_pencil_energy_mw(c->M, (int)n, nvv, c->mu2, dout, work, dinfo,
-                                                       one, c->stream);
+                                                       polls, c->stream);
     if (le == hipSuccess) le = hipMemcpyAsync(hp, dout, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (le == hipSuccess) le = hipMemcpyAsync(hp + 4, dinfo, 3 * sizeof(int), hipMemcpyDeviceToHost, c->stream);
     if (le == hipSuccess) le = hipStreamSynchronize(c->stream);
@@ -899,6 +899,14 @@ pprpa_status pprpa_dims(const pprpa_ctx* c, int64_t* n_pp, int64_t* n_hh) {
   if (!c) return einval("ctx is NULL");
   if (n_pp) *n_pp = c->g.nvv;
   if (n_hh) *n_hh = c->g.noo;
+  return PPRPA_OK;
+}
+
+// For the tests (not in the header): the polls after which this context's one-launch reductions give
+// up, 0 at once, negative: reductions by launches a step only.
+pprpa_status pprpa_test_tridiagonal_polls(pprpa_ctx* c, int32_t polls) {
+  if (!c) return einval("ctx is NULL");
+  c->tridiag_polls = polls;
   return PPRPA_OK;
 }
 
@@ -1058,16 +1066,17 @@ static pprpa_status nto_ab(pprpa_ctx* c, int k, const double* z, int on_device, 
   if (!on_device) le = hipMemcpyAsync((void*)dz, z, zv * sizeof(double), hipMemcpyHostToDevice, s);
   const bool sv = nto_spectra(nva), so = nto_spectra(noa);
   int* hl = (int*)c->pinned;
-  for (int one = 1; le == hipSuccess && one >= 0; --one) {
+  for (int polls : {c->tridiag_polls, -1}) {
+    if (le != hipSuccess) break;
     hl[0] = hl[1] = 0;
-    le = launch_nto_ab(dz, g.n, k, nva, nvb, noa, nob, Gx, Gy, Dv, Do, lp, lh, wk, lost, one, s);
+    le = launch_nto_ab(dz, g.n, k, nva, nvb, noa, nob, Gx, Gy, Dv, Do, lp, lh, wk, lost, polls, s);
     if (le == hipSuccess) le = hipMemcpyAsync(lam_p, lp, lv * sizeof(double), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && lo) le = hipMemcpyAsync(lam_h, lh, lo * sizeof(double), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && d_vv) le = hipMemcpyAsync(d_vv, Dv, dv * sizeof(double), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && d_oo && dov)
       le = hipMemcpyAsync(d_oo, Do, dov * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (le == hipSuccess && one && sv) le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
-    if (le == hipSuccess && one && so)
+    if (le == hipSuccess && polls >= 0 && sv) le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && polls >= 0 && so)
       le = hipMemcpyAsync(hl + 1, lost + 1, sizeof(int), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess) le = hipStreamSynchronize(s);
     if (!hl[0] && !hl[1]) break;  // (else: the one-launch reduction gave up, again without it)
@@ -1132,16 +1141,17 @@ pprpa_status pprpa_nto(pprpa_ctx* c, int32_t k, const double* z, int32_t on_devi
   if (!on_device) le = hipMemcpyAsync((void*)dz, z, zv * sizeof(double), hipMemcpyHostToDevice, s);
   const bool sv = nto_spectra(g.nv), so = nto_spectra(g.no);
   int* hl = (int*)c->pinned;
-  for (int one = 1; le == hipSuccess && one >= 0; --one) {
+  for (int polls : {c->tridiag_polls, -1}) {
+    if (le != hipSuccess) break;
     hl[0] = hl[1] = 0;
-    le = launch_nto(dz, g.n, k, g, c->ptab, X, Y, Gx, Gy, Dv, Do, lp, lh, wk, lost, one, s);
+    le = launch_nto(dz, g.n, k, g, c->ptab, X, Y, Gx, Gy, Dv, Do, lp, lh, wk, lost, polls, s);
     if (le == hipSuccess) le = hipMemcpyAsync(lam_p, lp, lv * sizeof(double), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && lo) le = hipMemcpyAsync(lam_h, lh, lo * sizeof(double), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && d_vv) le = hipMemcpyAsync(d_vv, Dv, mv * sizeof(double), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && d_oo && mo)
       le = hipMemcpyAsync(d_oo, Do, mo * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (le == hipSuccess && one && sv) le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
-    if (le == hipSuccess && one && so)
+    if (le == hipSuccess && polls >= 0 && sv) le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && polls >= 0 && so)
       le = hipMemcpyAsync(hl + 1, lost + 1, sizeof(int), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess) le = hipStreamSynchronize(s);
     if (!hl[0] && !hl[1]) break;  // (else: the one-launch reduction gave up, again without it)

@@ -40,6 +40,7 @@ struct pprpa_ctx {
   void* Lb = nullptr;              // staged beta integrals [naux][nmopb][nmopb] (L holds alpha)
   std::vector<int> ptab_h;
   std::atomic<int> busy{0};
+  int tridiag_polls = pprpa::TRIDIAG_POLLS;  // of its dense solves' one-launch reductions
   hipEvent_t e0 = nullptr, e1 = nullptr;
   double* pinned = nullptr;  // small pinned host buffer for per-iteration status
   size_t pinned_elems = 0;

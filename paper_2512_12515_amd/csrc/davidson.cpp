@@ -503,13 +503,13 @@ pprpa_status Solver::run_direct() {
   double* hp = c_->pinned;
   const int* info = (const int*)(hp + 128);
   if (m <= DENSE_ONE_WG_MAX) PPRPA_HIP(launch_metric_matrix(w.Ws_, n, nvv, s));
-  for (int one = 1; one >= 0; --one) {
+  for (int polls : {c_->tridiag_polls, -1}) {
     if (m <= DENSE_ONE_WG_MAX)  // W as a dense matrix: the Davidson pencil solver on the whole problem
       PPRPA_HIP(launch_pencil(c_->M, w.Ws_, m, m, c_->mu2, nroot_, nroot_, a_.channel, w.omega,
                               w.Cc, nroot_, w.pwork, w.info, s));
     else  // W diagonal, many workgroups
       PPRPA_HIP(launch_direct_pencil_mw(c_->M, m, nvv, c_->mu2, nroot_, a_.channel, w.omega, w.Cc,
-                                        nroot_, w.pwork, w.info, one, s));
+                                        nroot_, w.pwork, w.info, polls, s));
     PPRPA_HIP(launch_transpose(w.Cc, nroot_, m, nroot_, w.Z, n, s));
     PPRPA_HIP(launch_combine(c_->M, n, m, w.Cc, nroot_, nroot_, n, 1.0, 0.0, w.SZ, n, s));
     PPRPA_HIP(launch_residual(w.Z, w.SZ, n, nroot_, n, nvv, w.omega, w.R, w.part, 64, s));

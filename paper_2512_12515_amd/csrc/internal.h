@@ -224,10 +224,10 @@ hipError_t launch_pencil_energy(const double* M, int m, int64_t nvv, double mu2,
                                 double* work, int* info, hipStream_t s);
 // The same outputs as launch_pencil_energy for 32 <= m <= DENSE_ENERGY_MAX on many workgroups
 // (blocked Cholesky, S = L^T W L, Householder tridiagonal form, bisection; k_dense_mw.hip).
-// work: 3 m^2 doubles. one_launch: the tridiagonal form by launch_tridiag where it fits; info[0] = 4
-// when its workgroups lost one another (solve again without).
+// work: 3 m^2 doubles. polls: as of launch_tridiag, by which the tridiagonal form where it fits;
+// info[0] = 4 when its workgroups lost one another (solve again without). polls < 0: without it.
 hipError_t launch_pencil_energy_mw(const double* M, int m, int64_t nvv, double mu2, double* out,
-                                   double* work, int* info, bool one_launch, hipStream_t s);
+                                   double* work, int* info, int polls, hipStream_t s);
 // Direct solve of the dense pencil (M, W), W = diag(+1 for i < nvv, -1), for 32 <= m <=
 // DENSE_SOLVE_MAX on many workgroups (the chain of launch_pencil_energy_mw keeping its
 // reflections, multisection for the wanted eigenvalues, inverse iteration, back-transformation,
@@ -236,32 +236,34 @@ hipError_t launch_pencil_energy_mw(const double* M, int m, int64_t nvv, double m
 size_t direct_pencil_mw_work(int n, int nroot);
 hipError_t launch_direct_pencil_mw(const double* M, int m, int64_t nvv, double mu2, int nroot,
                                    int channel, double* omega, double* Cout, int ldc,
-                                   double* work, int* info, bool one_launch, hipStream_t s);
+                                   double* work, int* info, int polls, hipStream_t s);
 // Tridiagonal form (d, e) of nmat symmetric n x n matrices S (k_tridiag.hip), 3 <= n <= TRIDIAG_MAX
 // where tridiag_fits; X: exchange buffer of nmat tridiag_exchange(n) doubles. beta_keep (nmat = 1): the reflection
 // vectors stay in the rows of S right of the diagonal. *abort_flag: 0, or 1 when the workgroups
-// lost one another (the outputs are then not usable).
+// lost one another (the outputs are then not usable): one has waited for another for that many polls,
+// about 1 us each.
 constexpr int TRIDIAG_MAX = 2048;
+constexpr int TRIDIAG_POLLS = 1 << 21;
 bool tridiag_fits(int n);
 size_t tridiag_exchange(int n);
 hipError_t launch_tridiag(double* S, int n, int nmat, double* X, double* d, double* e,
-                          double* beta_keep, int* abort_flag, hipStream_t s);
+                          double* beta_keep, int* abort_flag, int polls, hipStream_t s);
 // Eigenvalues, descending and clamped at zero, of nmat symmetric n x n matrices S (destroyed) where
 // tridiag_fits(n): lam [nmat][n]. work: spectra_work(n, nmat) doubles; *lost as *abort_flag above.
 size_t spectra_work(int n, int nmat);
 hipError_t launch_spectra(double* S, int n, int nmat, double* lam, double* work, int* lost,
-                          hipStream_t s);
+                          int polls, hipStream_t s);
 // NTO weights and two-electron density blocks of k packed roots Z [k][ldz] (nv, no <= 512):
 // X [k][nv][nv], Y [k][no][no] (triangular amplitude matrices), Gx, Gy (their T^T T, destroyed),
 // Dv = X X^T + X^T X, Do = -(Y Y^T + Y^T Y) (may be null), lam_p [k][nv], lam_h [k][no]
-// (squared singular values, descending). work: nto_work(k, nv, no) doubles; one_launch: the
+// (squared singular values, descending). work: nto_work(k, nv, no) doubles; polls >= 0: the
 // eigenvalues of the blocks of order m with nto_spectra(m) by launch_spectra, lost [2] its flags for
-// the two blocks (set: launch again without).
+// the two blocks (set: launch again with polls < 0).
 bool nto_spectra(int m);
 size_t nto_work(int k, int nv, int no);
 hipError_t launch_nto(const double* Z, int64_t ldz, int k, const Geometry& g, const int* ptab,
                       double* X, double* Y, double* Gx, double* Gy, double* Dv, double* Do,
-                      double* lam_p, double* lam_h, double* work, int* lost, bool one_launch,
+                      double* lam_p, double* lam_h, double* work, int* lost, int polls,
                       hipStream_t s);
 // The same for k packed alpha-beta roots: X = nva x nvb and Y = noa x nob read in place from Z
 // (alpha index outer); Gx = X X^T [k][nva][nva], Gy = Y Y^T (destroyed); Dv [k][nva^2 + nvb^2]
@@ -270,7 +272,7 @@ hipError_t launch_nto(const double* Z, int64_t ldz, int k, const Geometry& g, co
 // nto_work(k, nva, noa) doubles.
 hipError_t launch_nto_ab(const double* Z, int64_t ldz, int k, int nva, int nvb, int noa, int nob,
                          double* Gx, double* Gy, double* Dv, double* Do, double* lam_p,
-                         double* lam_h, double* work, int* lost, bool one_launch, hipStream_t s);
+                         double* lam_h, double* work, int* lost, int polls, hipStream_t s);
 // The packed roots' triangular amplitude matrices X [k][nv][nv], Y [k][no][no] (zeros below).
 hipError_t launch_unpack_triangular(const double* Z, int64_t ldz, int k, const Geometry& g,
                                     const int* ptab, double* X, double* Y, hipStream_t s);

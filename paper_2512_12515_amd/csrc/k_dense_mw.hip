@@ -967,7 +967,7 @@ __global__ __launch_bounds__(256) void k_mw_vectors(const double* __restrict__ K
 // when K is not positive definite, or the reduction's workgroups lost one another.
 static hipError_t mw_reduce(const double* M, int n, int64_t nvv, double mu2, double* K, double* S,
                             double* X, double* v2, double* p, double* d, double* e, double* bsc,
-                            double* beta_keep, int* flag, int* lost, hipStream_t s) {
+                            double* beta_keep, int* flag, int* lost, int polls, hipStream_t s) {
   const size_t nn = (size_t)n * n;
   hipLaunchKernelGGL(k_mw_init, dim3(1), dim3(64), 0, s, flag, lost);
   hipLaunchKernelGGL(k_mw_shift, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, M, n, nvv,
@@ -985,7 +985,7 @@ static hipError_t mw_reduce(const double* M, int n, int64_t nvv, double mu2, dou
   const int ntile = (n + CB - 1) / CB;
   hipLaunchKernelGGL(k_mw_sym, dim3(ntile * (ntile + 1) / 2), dim3(256), 0, s, K, n, nvv, S);
   if (X && tridiag_fits(n)) {
-    const hipError_t rc = launch_tridiag(S, n, 1, X, d, e, beta_keep, lost, s);
+    const hipError_t rc = launch_tridiag(S, n, 1, X, d, e, beta_keep, lost, polls, s);
     if (rc != hipSuccess) return rc;
     hipLaunchKernelGGL(k_mw_bounds, dim3(1), dim3(1024), 0, s, (const double*)nullptr, n, d, e, bsc + 2,
                        v2);
@@ -1011,13 +1011,13 @@ size_t spectra_work(int n, int nmat) {
 }
 
 hipError_t launch_spectra(double* S, int n, int nmat, double* lam, double* work, int* lost,
-                          hipStream_t s) {
+                          int polls, hipStream_t s) {
   double* X = work;
   double* d = X + nmat * tridiag_exchange(n);
   double* e = d + (size_t)nmat * n;
   double* t2 = e + (size_t)nmat * n;
   double* bnd = t2 + nmat * sturm_elems(n);
-  const hipError_t rc = launch_tridiag(S, n, nmat, X, d, e, nullptr, lost, s);
+  const hipError_t rc = launch_tridiag(S, n, nmat, X, d, e, nullptr, lost, polls, s);
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL(k_mw_bounds, dim3(nmat), dim3(1024), 0, s, (const double*)nullptr, n, d, e, bnd, t2);
   hipLaunchKernelGGL((k_mw_bisect<64, true>), dim3((unsigned)((n + 3) / 4), nmat), dim3(256), 0, s, t2,
@@ -1026,7 +1026,7 @@ hipError_t launch_spectra(double* S, int n, int nmat, double* lam, double* work,
 }
 
 hipError_t launch_pencil_energy_mw(const double* M, int n, int64_t nvv, double mu2, double* out,
-                                   double* work, int* info, bool one_launch, hipStream_t s) {
+                                   double* work, int* info, int polls, hipStream_t s) {
   if (n < 32 || n > DENSE_ENERGY_MAX) return hipErrorInvalidValue;
   const size_t nn = (size_t)n * n;
   double* S = work;
@@ -1037,9 +1037,10 @@ hipError_t launch_pencil_energy_mw(const double* M, int n, int64_t nvv, double m
   double* lam = e + n;
   double* bsc = lam + n;  // [0], [1] beta, [2 .. 4] Gershgorin bounds and norm
   double* K = bsc + 8;    // and, once S is formed, with the rest of work the exchange buffer
-  double* X = one_launch && K + tridiag_exchange(n) <= work + 3 * nn ? K : nullptr;
+  double* X = polls >= 0 && K + tridiag_exchange(n) <= work + 3 * nn ? K : nullptr;
   int* flag = info;  // info[0], info[1] double as the flags until the last kernel
-  const hipError_t rc = mw_reduce(M, n, nvv, mu2, K, S, X, v2, p, d, e, bsc, nullptr, flag, info + 1, s);
+  const hipError_t rc = mw_reduce(M, n, nvv, mu2, K, S, X, v2, p, d, e, bsc, nullptr, flag, info + 1,
+                                  polls, s);
   if (rc != hipSuccess) return rc;
   if (n <= 4096)
     hipLaunchKernelGGL((k_mw_bisect<64, false>), dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, v2, n,
@@ -1058,7 +1059,7 @@ size_t direct_pencil_mw_work(int n, int nroot) {
 
 hipError_t launch_direct_pencil_mw(const double* M, int n, int64_t nvv, double mu2, int nroot,
                                    int channel, double* omega, double* Cout, int ldc,
-                                   double* work, int* info, bool one_launch, hipStream_t s) {
+                                   double* work, int* info, int polls, hipStream_t s) {
   if (n < 32 || n > DENSE_SOLVE_MAX || nroot < 1 || nroot > 64 || nroot > n || ldc < nroot ||
       (channel != 0 && channel != 1))
     return hipErrorInvalidValue;
@@ -1078,8 +1079,8 @@ hipError_t launch_direct_pencil_mw(const double* M, int n, int64_t nvv, double m
   int* cnt = (int*)(bsc + 8);         // [0] eigenvalues below 0
   int* flag = cnt + 1;                // K not positive definite
   int* lost = cnt + 2;                // the reduction's workgroups lost one another
-  const hipError_t rc = mw_reduce(M, n, nvv, mu2, K, S, one_launch ? X : nullptr, v2, p, d, e, bsc,
-                                  beta, flag, lost, s);
+  const hipError_t rc = mw_reduce(M, n, nvv, mu2, K, S, polls >= 0 ? X : nullptr, v2, p, d, e, bsc,
+                                  beta, flag, lost, polls, s);
   if (rc != hipSuccess) return rc;
   hipLaunchKernelGGL(k_mw_select, dim3(nroot), dim3(256), 0, s, v2, n, bsc + 2, cnt, channel, flag,
                      lam);

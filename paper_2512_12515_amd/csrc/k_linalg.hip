@@ -1687,15 +1687,15 @@ size_t nto_work(int k, int nv, int no) {
 }
 
 static hipError_t gram_eigenvalues(double* G, int m, int k, double* lam, double* work, int* lost,
-                                   bool one_launch, hipStream_t s) {
-  if (one_launch && nto_spectra(m)) return launch_spectra(G, m, k, lam, work, lost, s);
+                                   int polls, hipStream_t s) {
+  if (polls >= 0 && nto_spectra(m)) return launch_spectra(G, m, k, lam, work, lost, polls, s);
   hipLaunchKernelGGL(k_gram_eigenvalues, dim3(k), dim3(WG), 0, s, G, m, lam);
   return hipGetLastError();
 }
 
 hipError_t launch_nto_ab(const double* Z, int64_t ldz, int k, int nva, int nvb, int noa, int nob,
                          double* Gx, double* Gy, double* Dv, double* Do, double* lam_p,
-                         double* lam_h, double* work, int* lost, bool one_launch, hipStream_t s) {
+                         double* lam_h, double* work, int* lost, int polls, hipStream_t s) {
   if (k < 1 || nva > JMAX || nvb > JMAX || noa > JMAX || nob > JMAX) return hipErrorInvalidValue;
   const int64_t nvv = (int64_t)nva * nvb;
   const int64_t ev = (int64_t)nva * nva + (int64_t)nvb * nvb;
@@ -1703,20 +1703,20 @@ hipError_t launch_nto_ab(const double* Z, int64_t ldz, int k, int nva, int nvb, 
                      ldz, (int64_t)0, nva, nvb, 1.0, Gx, Dv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((e = gram_eigenvalues(Gx, nva, k, lam_p, work, lost, one_launch, s)) != hipSuccess) return e;
+  if ((e = gram_eigenvalues(Gx, nva, k, lam_p, work, lost, polls, s)) != hipSuccess) return e;
   if (noa > 0) {
     const int64_t eo = (int64_t)noa * noa + (int64_t)nob * nob;
     hipLaunchKernelGGL(k_rect_products, dim3((unsigned)((eo + NT - 1) / NT), k), dim3(NT), 0, s,
                        Z, ldz, nvv, noa, nob, -1.0, Gy, Do);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = gram_eigenvalues(Gy, noa, k, lam_h, work, lost + 1, one_launch, s);
+    e = gram_eigenvalues(Gy, noa, k, lam_h, work, lost + 1, polls, s);
   }
   return e;
 }
 
 hipError_t launch_nto(const double* Z, int64_t ldz, int k, const Geometry& g, const int* ptab,
                       double* X, double* Y, double* Gx, double* Gy, double* Dv, double* Do,
-                      double* lam_p, double* lam_h, double* work, int* lost, bool one_launch,
+                      double* lam_p, double* lam_h, double* work, int* lost, int polls,
                       hipStream_t s) {
   if (k < 1 || g.nv > JMAX || g.no > JMAX) return hipErrorInvalidValue;
   const size_t xv = (size_t)k * g.nv * g.nv, yo = (size_t)k * g.no * g.no;
@@ -1730,12 +1730,12 @@ hipError_t launch_nto(const double* Z, int64_t ldz, int k, const Geometry& g, co
   hipLaunchKernelGGL(k_triangular_products, dim3(tv * (tv + 1) / 2, k), dim3(256), 0, s, X, g.nv, 1.0,
                      Gx, Dv);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = gram_eigenvalues(Gx, g.nv, k, lam_p, work, lost, one_launch, s)) != hipSuccess) return e;
+  if ((e = gram_eigenvalues(Gx, g.nv, k, lam_p, work, lost, polls, s)) != hipSuccess) return e;
   if (g.no > 0) {
     hipLaunchKernelGGL(k_triangular_products, dim3(to * (to + 1) / 2, k), dim3(256), 0, s, Y, g.no,
                        -1.0, Gy, Do);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = gram_eigenvalues(Gy, g.no, k, lam_h, work, lost + 1, one_launch, s);
+    e = gram_eigenvalues(Gy, g.no, k, lam_h, work, lost + 1, polls, s);
   }
   return e;
 }

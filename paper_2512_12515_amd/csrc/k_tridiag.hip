@@ -33,8 +33,9 @@
 // workgroups' stores of steps before k only, the workgroups of a launch fit the chip at once (at
 // most one per compute unit), and launches of different streams are ordered one after the other
 // (launch_tridiag). Several processes on one device can still each hold a part of it and wait for
-// the rest: a poll that does not end within some seconds gives up, it raises the abort flag, which
-// every poll reads, and the host solves again by launches a step.
+// the rest: a poll that does not end within TRIDIAG_POLLS tries (some seconds) gives up, it raises the
+// abort flag, which every poll reads, and the host solves again by launches a step. (With no tries at
+// all every workgroup gives up at its first poll: how the tests reach that.)
 #include <algorithm>
 #include <mutex>
 
@@ -49,7 +50,6 @@ constexpr u64 EMPTY = 0x7FF4B1DFACE50DADull;  // a NaN; no operation produces th
 constexpr u64 OTHER_NAN = 0x7FF8000000000000ull;
 constexpr double NORM2_MIN = 0x1p-960;  // squared norm below which a row counts as 0
 constexpr int TW = 8;                 // waves per workgroup
-constexpr int POLL_LIMIT = 1 << 21;   // polls (about 1 us each) before giving up
 
 __device__ __forceinline__ void publish(double* p, double v) {
   u64 b = (u64)__double_as_longlong(v);
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(64 * TW, 2) void k_tridiag(double* __restrict__ Sal
                                                         double* __restrict__ dall,
                                                         double* __restrict__ eall,
                                                         double* __restrict__ beta_keep,
-                                                        int* __restrict__ abort_flag) {
+                                                        int* __restrict__ abort_flag, int polls) {
   constexpr int N = 64 * CPL, NT = 64 * TW, E = (N + NT - 1) / NT, RPG = TW * RPW;
   // x: the next reflection's vector but for its first element (by parity of the step); bc: p and v
   // at k + 1, x at k + 2
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(64 * TW, 2) void k_tridiag(double* __restrict__ Sal
     // 2. p and row k + 1 at this thread's columns
     u64 pb[E], rb[E];
     for (int tries = 1;; ++tries) {
-      bool miss = false;
+      bool miss = polls == 0;
 #pragma unroll
       for (int q = 0; q < E; ++q) {
         const int c = t + NT * q;
@@ -201,8 +201,8 @@ __global__ __launch_bounds__(64 * TW, 2) void k_tridiag(double* __restrict__ Sal
 #pragma unroll
       for (int q = 0; q < E; ++q) miss |= pb[q] == EMPTY || rb[q] == EMPTY;
       if (!miss) break;
-      if ((tries & 1023) == 0) {
-        if (tries >= POLL_LIMIT) __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((tries & 1023) == 0 || polls == 0) {
+        if (tries >= polls) __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (__hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
           dead = 1;
           break;
@@ -324,7 +324,7 @@ int groups(int n, int rpw) { return (n + TW * rpw - 1) / (TW * rpw); }
 
 template <int CPL, int RPW>
 hipError_t run(double* S, int n, int nmat, double* X, double* d, double* e, double* beta_keep,
-               int* abort_flag, int cus, hipStream_t s) {
+               int* abort_flag, int polls, int cus, hipStream_t s) {
   const int G = groups(n, RPW);
   const size_t ldx = tridiag_exchange(n);
   const int batch = cus / G;  // matrices per launch
@@ -332,7 +332,7 @@ hipError_t run(double* S, int n, int nmat, double* X, double* d, double* e, doub
     const int nb = nmat - m0 < batch ? nmat - m0 : batch;
     const size_t off = (size_t)m0 * n;
     hipLaunchKernelGGL((k_tridiag<CPL, RPW>), dim3(nb * G), dim3(64 * TW), 0, s, S + off * n, n, G,
-                       X + m0 * ldx, ldx, d + off, e + off, beta_keep, abort_flag);
+                       X + m0 * ldx, ldx, d + off, e + off, beta_keep, abort_flag, polls);
   }
   return hipGetLastError();
 }
@@ -343,12 +343,12 @@ hipError_t run(double* S, int n, int nmat, double* X, double* d, double* e, doub
 // row's product and the sums over columns do not depend on it.
 template <int CPL, int MOST>
 hipError_t run_rows(double* S, int n, int nmat, double* X, double* d, double* e, double* beta_keep,
-                    int* abort_flag, int cus, hipStream_t s) {
+                    int* abort_flag, int polls, int cus, hipStream_t s) {
   if ((int64_t)nmat * groups(n, 1) <= cus)
-    return run<CPL, 1>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
+    return run<CPL, 1>(S, n, nmat, X, d, e, beta_keep, abort_flag, polls, cus, s);
   if (MOST == 2 || (int64_t)nmat * groups(n, 2) <= cus)
-    return run<CPL, 2>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
-  return run<CPL, MOST>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
+    return run<CPL, 2>(S, n, nmat, X, d, e, beta_keep, abort_flag, polls, cus, s);
+  return run<CPL, MOST>(S, n, nmat, X, d, e, beta_keep, abort_flag, polls, cus, s);
 }
 
 }  // namespace
@@ -367,12 +367,12 @@ size_t tridiag_exchange(int n) {
 }
 
 hipError_t launch_tridiag(double* S, int n, int nmat, double* X, double* d, double* e,
-                          double* beta_keep, int* abort_flag, hipStream_t s) {
+                          double* beta_keep, int* abort_flag, int polls, hipStream_t s) {
   int dev = 0, cus = 0;
   hipError_t rc = hipGetDevice(&dev);
   if (rc == hipSuccess) rc = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (rc != hipSuccess) return rc;
-  if (!tridiag_fits(n) || nmat < 1 || (beta_keep && nmat > 1)) return hipErrorInvalidValue;
+  if (!tridiag_fits(n) || nmat < 1 || polls < 0 || (beta_keep && nmat > 1)) return hipErrorInvalidValue;
   Gate& gt = g_gate[dev];
   std::lock_guard<std::mutex> lk(gt.mu);
   if (!gt.last) {
@@ -382,10 +382,10 @@ hipError_t launch_tridiag(double* S, int n, int nmat, double* X, double* d, doub
   }
   const size_t total = nmat * tridiag_exchange(n), blocks = std::min<size_t>((total + 1023) / 1024, 2048);
   hipLaunchKernelGGL(k_tridiag_clear, dim3((unsigned)blocks), dim3(256), 0, s, X, total, abort_flag);
-  rc = n <= 256   ? run_rows<4, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
-       : n <= 512 ? run_rows<8, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
-       : n <= 1088 ? run_rows<17, 2>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s)
-                   : run<32, 1>(S, n, nmat, X, d, e, beta_keep, abort_flag, cus, s);
+  rc = n <= 256   ? run_rows<4, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, polls, cus, s)
+       : n <= 512 ? run_rows<8, 4>(S, n, nmat, X, d, e, beta_keep, abort_flag, polls, cus, s)
+       : n <= 1088 ? run_rows<17, 2>(S, n, nmat, X, d, e, beta_keep, abort_flag, polls, cus, s)
+                   : run<32, 1>(S, n, nmat, X, d, e, beta_keep, abort_flag, polls, cus, s);
   if (rc == hipSuccess) rc = hipEventRecord(gt.last, s);
   return rc;
 }
