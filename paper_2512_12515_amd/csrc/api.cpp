@@ -154,6 +154,8 @@ static pprpa_status gated_launch(pprpa_ctx* c, pprpa_ctx::Timed& tm, F&& launch)
 }
 
 pprpa_status sigma_device(pprpa_ctx* c, int k, const double* dz, double* ds) {
+  if (!c->Sp && c->sp_least > 0)  // (malloc_giving_back)
+    PPRPA_TRY(dalloc(c, c->sp_least * c->sp_bytes, &c->Sp));
   const int64_t n = c->g.n;
   if (c->ab && c->ab_df) {  // density-fitted alpha-beta sector
     const AbGeometry& ag = c->abg;
@@ -235,11 +237,24 @@ struct Busy {
   }
 };
 
+// Sigma workspace beyond the least held by the contexts of each device, bytes.
+std::atomic<size_t> g_more[GATE_DEVICES];
+
+// Releases a workspace of more than the least (c->Sp is null then).
+void free_more(pprpa_ctx* c) {
+  if (!c->Sp || c->sp_slots == c->sp_least) return;
+  (void)hipFree(c->Sp);
+  g_more[c->device].fetch_sub((c->sp_slots - c->sp_least) * c->sp_bytes);
+  c->Sp = nullptr;
+  c->sp_slots = c->sp_least;
+}
+
 void destroy(pprpa_ctx* c) {
   if (!c) return;
   int cur = 0;
   if (hipGetDevice(&cur) == hipSuccess && cur != c->device) (void)hipSetDevice(c->device);
   if (c->stream) (void)hipStreamSynchronize(c->stream);
+  free_more(c);
   for (void* p : c->allocs) (void)hipFree(p);
   if (c->dws.base && !c->slab) (void)hipFree(c->dws.base);
   if (c->pinned && c->own_pinned) (void)hipHostFree(c->pinned);
@@ -314,15 +329,28 @@ pprpa_status setup_runtime(pprpa_ctx* c, void* stream) {
 
 // Partial sums of a sigma launch: at least `slots` matrices of `bytes` each. A context that runs the
 // two-product form outside a slab takes up to MM_WORKSPACE bytes instead, so that its products need
-// fewer, longer launches; it does with the least when that much is not free. A dense context (least),
-// built for the direct solve, does too: the larger allocation is a third of its build at 5/20/100.
+// fewer, longer launches. No context or solve is refused for it: this is the context's last allocation,
+// the least does when the rest is not free, and a later allocation of the context's that is refused gets
+// the rest. A dense context (least), built for the direct solve, does without.
 pprpa_status alloc_sums(pprpa_ctx* c, const MmGeometry& mg, size_t slots, size_t bytes, bool least) {
-  c->sp_slots = (int64_t)slots;
-  if (!c->slab && !least && mm_plan(c->st, mg, c->kcap, nsplit_for(c, c->kcap) * c->kcap).nslot > 0) {
-    const size_t more = std::min(slots + (size_t)mg.naux * c->kcap, MM_WORKSPACE / bytes);
-    if (more > slots && dalloc(c, more * bytes, &c->Sp) == PPRPA_OK) {
-      c->sp_slots = (int64_t)more;
-      return PPRPA_OK;
+  c->sp_slots = c->sp_least = (int64_t)slots;
+  c->sp_bytes = bytes;
+  if (!c->slab && !least && slots * bytes > MM_WORKSPACE_MIN && c->device >= 0 && c->device < GATE_DEVICES &&
+      mm_plan(c->st, mg, c->kcap, nsplit_for(c, c->kcap) * c->kcap).nslot > 0) {
+    size_t free_now = 0, total = 0;
+    if (hipMemGetInfo(&free_now, &total) != hipSuccess) (void)hipGetLastError();
+    const size_t most = std::min(MM_WORKSPACE, free_now / MM_WORKSPACE_SHARE);
+    const size_t want = std::min(slots + (size_t)mg.naux * c->kcap, most / bytes);
+    if (want > slots) {
+      const size_t more = (want - slots) * bytes;
+      if (g_more[c->device].fetch_add(more) + more <= MM_WORKSPACE_MORE &&
+          hipMalloc(&c->Sp, want * bytes) == hipSuccess) {
+        c->sp_slots = (int64_t)want;
+        return PPRPA_OK;
+      }
+      (void)hipGetLastError();
+      c->Sp = nullptr;
+      g_more[c->device].fetch_sub(more);
     }
   }
   return dalloc(c, slots * bytes, &c->Sp);
@@ -468,7 +496,6 @@ pprpa_status build_impl(const pprpa_build_args* a, pprpa_ctx* c) {
   PPRPA_TRY(dalloc(c, c->zplane * esz * nplanes, &c->ZT));
   PPRPA_HIP(hipMemsetAsync(c->ZT, 0, c->zplane * esz * nplanes, c->stream));
   const size_t spsz = c->st == Store::F64 ? 8 : 4;
-  PPRPA_TRY(alloc_sums(c, mm_geometry(g), sp_max, zz * spsz, a->dense != 0));
   PPRPA_TRY(dalloc(c, (size_t)c->kcap * g.n * sizeof(double), (void**)&c->zbuf));
   PPRPA_TRY(dalloc(c, (size_t)c->kcap * g.n * sizeof(double), (void**)&c->sbuf));
 
@@ -478,6 +505,7 @@ pprpa_status build_impl(const pprpa_build_args* a, pprpa_ctx* c) {
     PPRPA_TRY(dalloc(c, (size_t)g.n * g.n * sizeof(double), (void**)&c->M));
     PPRPA_HIP(launch_dense_build(g, c->L64, c->ptab, c->epair, c->M, c->stream));
   }
+  PPRPA_TRY(alloc_sums(c, mm_geometry(g), sp_max, zz * spsz, a->dense != 0));
   PPRPA_HIP(hipStreamSynchronize(c->stream));
   return PPRPA_OK;
 }
@@ -634,11 +662,6 @@ pprpa_status build_ab_impl(const pprpa_build_ab_args* a, pprpa_ctx* c) {
     PPRPA_TRY(dalloc(c, items.size() * sizeof(int), (void**)&c->plan.d_items));
     PPRPA_HIP(hipMemcpyAsync(c->plan.d_items, items.data(), items.size() * sizeof(int),
                              hipMemcpyHostToDevice, c->stream));
-    size_t sp_max = 0;
-    for (int kk = 1; kk <= c->kcap; ++kk)
-      sp_max = std::max(sp_max, (size_t)nsplit_for(c, kk) * kk);
-    PPRPA_TRY(alloc_sums(c, mm_geometry(ag), sp_max,
-                         (size_t)ag.nmopa * ag.nmopb * (c->st == Store::F64 ? 8 : 4), false));
   } else {
     PPRPA_TRY(dalloc(c, (size_t)g.n * g.n * sizeof(double), (void**)&c->M));
     PPRPA_HIP(launch_dense_build_ab(La, Lb, naux, nmo, noa, nob, g.n, g.nvv, c->ptab, c->epair,
@@ -646,6 +669,14 @@ pprpa_status build_ab_impl(const pprpa_build_ab_args* a, pprpa_ctx* c) {
   }
   PPRPA_TRY(dalloc(c, (size_t)c->kcap * g.n * sizeof(double), (void**)&c->zbuf));
   PPRPA_TRY(dalloc(c, (size_t)c->kcap * g.n * sizeof(double), (void**)&c->sbuf));
+  if (c->ab_df) {
+    const AbGeometry& ag = c->abg;
+    size_t sp_max = 0;
+    for (int kk = 1; kk <= c->kcap; ++kk)
+      sp_max = std::max(sp_max, (size_t)nsplit_for(c, kk) * kk);
+    PPRPA_TRY(alloc_sums(c, mm_geometry(ag), sp_max,
+                         (size_t)ag.nmopa * ag.nmopb * (c->st == Store::F64 ? 8 : 4), false));
+  }
   int bad = 0;
   PPRPA_HIP(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   PPRPA_HIP(hipStreamSynchronize(c->stream));
@@ -656,6 +687,21 @@ pprpa_status build_ab_impl(const pprpa_build_ab_args* a, pprpa_ctx* c) {
 }  // namespace
 
 namespace pprpa {
+
+hipError_t malloc_giving_back(pprpa_ctx* c, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess || !c->Sp || c->sp_slots == c->sp_least) return e;
+  (void)hipGetLastError();
+  if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
+  free_more(c);
+  if (hipMalloc(&c->Sp, c->sp_least * c->sp_bytes) != hipSuccess) {  // (the next product tries again)
+    (void)hipGetLastError();
+    c->Sp = nullptr;
+  } else {
+    c->allocs.push_back(c->Sp);
+  }
+  return hipMalloc(p, bytes);
+}
 
 pprpa_status check_build_args(const pprpa_build_args* a) {
   if (!a) return einval("args is NULL");
@@ -990,7 +1036,7 @@ pprpa_status pprpa_correlation_energy(pprpa_ctx* c, pprpa_corr_energy* out) {
   const int64_t n = c->g.n;
   const size_t work_bytes = 3 * (size_t)n * n * sizeof(double) + 256;
   void* work = nullptr;
-  hipError_t e = hipMalloc(&work, work_bytes);
+  hipError_t e = malloc_giving_back(c, &work, work_bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     set_error("correlation-energy workspace of %zu bytes: %s", work_bytes, hipGetErrorString(e));
@@ -1041,7 +1087,7 @@ static pprpa_status nto_ab(pprpa_ctx* c, int k, const double* z, int on_device, 
   const size_t wl = nto_work(k, nva, noa);
   const size_t total = (on_device ? 0 : zv) + gv + go + dv + dov + lv + lo + wl + 1;
   double* buf = nullptr;
-  hipError_t e = hipMalloc((void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
+  hipError_t e = malloc_giving_back(c, (void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
   if (e != hipSuccess) {
     (void)hipGetLastError();
     set_error("NTO workspace of %zu bytes: %s", total * sizeof(double), hipGetErrorString(e));
@@ -1114,7 +1160,7 @@ pprpa_status pprpa_nto(pprpa_ctx* c, int32_t k, const double* z, int32_t on_devi
   const size_t wl = nto_work(k, g.nv, g.no);
   const size_t total = (on_device ? 0 : zv) + 3 * mv + 3 * mo + lv + lo + wl + 1;
   double* buf = nullptr;
-  hipError_t e = hipMalloc((void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
+  hipError_t e = malloc_giving_back(c, (void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
   if (e != hipSuccess) {
     (void)hipGetLastError();
     set_error("NTO workspace of %zu bytes: %s", total * sizeof(double), hipGetErrorString(e));
@@ -1194,7 +1240,7 @@ pprpa_status pprpa_nto_vectors(pprpa_ctx* c, int32_t k, const double* z, int32_t
   const size_t op = (size_t)k * nvec * ((size_t)rp + cp), oh = hh ? (size_t)k * nvec * ((size_t)rh + ch) : 0;
   const size_t total = (on_device ? 0 : zv) + xs + std::max(wp, wh) + op + oh;
   double* buf = nullptr;
-  hipError_t e = hipMalloc((void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
+  hipError_t e = malloc_giving_back(c, (void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
   if (e != hipSuccess) {
     (void)hipGetLastError();
     set_error("NTO workspace of %zu bytes: %s", total * sizeof(double), hipGetErrorString(e));

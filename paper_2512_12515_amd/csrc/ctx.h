@@ -25,7 +25,9 @@ struct pprpa_ctx {
   void* ZT = nullptr;       // unpacked vectors [kcap][nmop][nmop] (3 planes for BF16)
   size_t zplane = 0;
   void* Sp = nullptr;       // sigma partial sums (and workspace of the two-product form)
-  int64_t sp_slots = 0;     // its size in nmop x nmop matrices of the sigma precision
+  int64_t sp_slots = 0;     // its size in matrices (nmop x nmop of the sigma precision), the least
+  int64_t sp_least = 0;     // that every product needs, and the bytes of one
+  size_t sp_bytes = 0;
   double* zbuf = nullptr;   // [kcap][n] staging of host vectors
   double* sbuf = nullptr;
   double* M = nullptr;      // dense matrix [n][n] (dense builds)
@@ -71,6 +73,9 @@ int nsplit_for(const pprpa_ctx* c, int k);
 int nsplit_of(const SigmaPlan& plan, int naux, int k);
 
 pprpa_status dalloc(pprpa_ctx* c, size_t bytes, void** p);
+// hipMalloc outside a slab; where it is refused, the context goes down to its least sigma workspace and it
+// is tried again.
+hipError_t malloc_giving_back(pprpa_ctx* c, void** p, size_t bytes);
 // Fold completed launch timings into c->stats (call after synchronising the stream).
 pprpa_status harvest_timing(pprpa_ctx* c);
 // Served contexts (the serving loop): argument checks shared with pprpa_build; exact device

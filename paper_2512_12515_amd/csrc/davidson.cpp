@@ -126,7 +126,7 @@ pprpa_status get_ws(pprpa_ctx* c, int mmax, int nret, int blk, size_t pwork_elem
       if (c->dws.base) (void)hipFree(c->dws.base);
       c->dws.base = nullptr;
       c->dws.bytes = 0;
-      hipError_t e = hipMalloc(&c->dws.base, total);
+      hipError_t e = malloc_giving_back(c, &c->dws.base, total);
       if (e != hipSuccess) {
         (void)hipGetLastError();
         c->dws.base = nullptr;

@@ -564,7 +564,7 @@ static hipError_t run_mm(const MmGeometry& g, const MmPlan& m, const void* La, c
   p.lbstride = (int64_t)p.nmopb * p.nmopb;
   p.qstride = (int64_t)p.nmopa * p.nmopb;
   p.qostride = (int64_t)(g.ncta - g.nvta) * (g.nctb - g.nvtb) * TILE * TILE;
-    p.Q = (double*)ws;
+  p.Q = (double*)ws;
   p.Qo = p.Q + (int64_t)m.nslot * k * p.qstride;
   // parts of T: all of it in one buffer, or as much as two hold
   const int len = (g.naux + m.nslot - 1) / m.nslot;  // longest slot

@@ -29,10 +29,19 @@ constexpr double BF_MIN_FILL = 0.8;
 // Fewest aux indices: below, the one-kernel form has a split for every aux index whatever the block
 // width, and a vector's sigma does not depend on the block around it; that stays so.
 constexpr int MM_MIN_NAUX = 96;
-// Workspace that a context outside a slab takes at most (20/200/700, 20 vectors: 8610 us with the
-// least workspace, 7902 with 2 GB, 7679 with 4 GB, 8097 with 8 GB, where the phases no longer share
-// launches).
-constexpr size_t MM_WORKSPACE = size_t(4) << 30;
+// Workspace that a context outside a slab takes at most, where its least is over MM_WORKSPACE_MIN. FP64 products
+// with the least / 1 GB / 1536 MB / 4 GB, us: 20/200/700, 20 vectors 8435 / 8293 / 7881 / 7740, 10 vectors
+// 4364 / 4251 / 4100 / 3964; 13/117/457, 7 vectors 685 / 546 / 561 / 547. hipMalloc and hipFree of one
+// buffer take 24 us up to 64 MB, 0.3 ms up to 1536 MB, 0.57 ms at 2 GB and 90 to 120 ms from 3 GB on (some
+// hipMallocs after such a hipFree as long), and a build with its release 0.87 ms (13/117/457) and 1.1 ms
+// (20/200/700) up to 1536 MB, 1.2 and 1.4 ms with 4 GB. At 5/20/100 (59 MB) more is no faster.
+constexpr size_t MM_WORKSPACE = size_t(1536) << 20;
+constexpr size_t MM_WORKSPACE_MIN = size_t(64) << 20;
+// What all contexts of the process take beyond their least on a device, and the share of the device's free
+// memory that one takes in all: a program with many contexts, or with little memory left, keeps nearly
+// all of it for its own.
+constexpr size_t MM_WORKSPACE_MORE = size_t(8) << 30;
+constexpr size_t MM_WORKSPACE_SHARE = 16;
 
 // Alpha (rows, c) and beta (d, columns) tiles, virtual block first; a restricted context has both
 // alike and takes the upper triangle of U (tri).

@@ -1,0 +1,98 @@
+"""The sigma workspace beyond the least that a context takes for the two-product form: it is bounded, over
+all contexts too, it leaves no trace where it is refused, it is given back to a later allocation of the
+context's that is refused otherwise, and no result depends on it."""
+import numpy as np
+import pytest
+
+from workloads import gen
+import paper_2512_12515_amd as P
+
+pytestmark = pytest.mark.gpu
+
+MB = 1 << 20
+MOST, ALL = 1536 * MB, 8192 * MB  # a context's workspace, what all take beyond their least
+
+
+def free_memory():
+    import torch
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def on_device(seed, nocc, nvir, naux):
+    import torch
+    idx = np.arange(nocc + nvir)
+    dev = torch.device("cuda:0")
+    L = gen.lpq_block_torch(seed, nocc + nvir, naux, idx, idx, np.arange(naux), dev)
+    eps = torch.from_numpy(gen.orbital_energies(seed, nocc, nvir)).to(dev)
+    torch.cuda.synchronize()
+    return eps, L
+
+
+def test_many_contexts_take_a_bounded_workspace():
+    import torch
+    nocc, nvir, naux = 13, 117, 457
+    eps, L = on_device(3, nocc, nvir, naux)
+    z = None
+    ctxs, used, results = [], [], []
+    try:
+        for i in range(14):
+            print("context", i, flush=True)
+            before = free_memory()
+            ctx = P.PpRPA(eps, L, nocc)
+            ctxs.append(ctx)
+            assert P.binding.lib().pprpa_last_error() == b""
+            used.append(before - free_memory())
+            if z is None:
+                z = torch.from_numpy(gen.random_vectors(4, 20, ctx.n)).to(L.device)
+            results.append(ctx.matvec(z).cpu().numpy())
+    finally:
+        for ctx in ctxs:
+            ctx.close()
+    least = min(used)
+    assert max(used) <= least + MOST and sum(u - least for u in used) <= ALL + 14 * 64 * MB
+    assert max(used) > least + 512 * MB  # (some have more than the least, the last do not)
+    assert used[-1] <= least + 64 * MB
+    for r in results[1:]:
+        assert np.array_equal(r, results[0])
+    with P.PpRPA(eps, L, nocc) as ctx:  # closed contexts have given theirs back
+        assert np.array_equal(ctx.matvec(z).cpu().numpy(), results[0])
+        assert free_memory() < before + sum(used) - least - 512 * MB
+
+
+@pytest.mark.parametrize("prec", ["fp64", "bf16x6"])
+def test_refused_solver_workspace_gets_the_rest(prec):
+    """The solver's workspace (410 MB) does not fit beside a context that has all its workspace, but fits
+    once that is down to the least."""
+    import torch
+    nocc, nvir, naux = 20, 300, 110
+    eps, L = on_device(5, nocc, nvir, naux)
+    L = 0.2 * L  # (a definite pencil at this size)
+    torch.cuda.synchronize()
+    with P.PpRPA(eps, L, nocc, prec=prec) as ctx:
+        z = torch.from_numpy(gen.random_vectors(6, 20, ctx.n)).to(L.device)
+        before = ctx.matvec(z).cpu().numpy()
+        solve = dict(tol=1e-3, block=16, max_subspace=256, max_iter=3)
+        with P.PpRPA(eps, L, nocc, prec=prec) as other:
+            ref = other.matvec(z).cpu().numpy()
+            try:
+                other.davidson(8, **solve)
+            except P.PpRPAError as e:
+                assert e.status == P.binding.ENOCONV
+        torch.cuda.empty_cache()
+        fill = []
+        while free_memory() > 400 * MB and len(fill) < 8:
+            fill.append(torch.empty(free_memory() - 300 * MB, dtype=torch.uint8, device=L.device))
+        left = free_memory()
+        print("filled, free MB", left // MB, flush=True)
+        assert left <= 400 * MB
+        try:
+            ctx.davidson(8, **solve)
+        except P.PpRPAError as e:
+            assert e.status == P.binding.ENOCONV, str(e)
+        print("solved, free MB", free_memory() // MB, flush=True)
+        assert free_memory() > left
+        after = ctx.matvec(z).cpu().numpy()
+        del fill
+        torch.cuda.empty_cache()
+    assert np.array_equal(before, ref) and np.array_equal(after, ref)
