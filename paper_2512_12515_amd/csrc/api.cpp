@@ -79,9 +79,9 @@ pprpa_status dalloc(pprpa_ctx* c, size_t bytes, void** p) {
 
 // Aux-index splits of a sigma launch of the one-kernel form: about 8192 workgroups (32 per CU),
 // which measured best on MI355X (shorter tails and better balance than 1.5k-4k; partial sums stay
-// small).
+// small), twice that of the pipelined FP64 kernel's, one workgroup per CU.
 int nsplit_of(const SigmaPlan& plan, int naux, int k) {
-  const int per = std::max(1, plan.unit_items * k);
+  const int per = std::max(1, plan.nitems * k);
   int ns = (plan.units + per - 1) / per;
   ns = std::min(ns, std::min(naux, 256));
   return std::max(1, ns);
@@ -658,7 +658,7 @@ pprpa_status build_ab_impl(const pprpa_build_ab_args* a, pprpa_ctx* c) {
     PPRPA_HIP(hipMemsetAsync(c->ZT, 0, zt * esz * nplanes, c->stream));
     std::vector<int> items;
     make_sigma_items_ab(ag, items, c->plan.npan_v);
-    c->plan.nitems = c->plan.unit_items = (int)items.size();
+    c->plan.nitems = (int)items.size();
     PPRPA_TRY(dalloc(c, items.size() * sizeof(int), (void**)&c->plan.d_items));
     PPRPA_HIP(hipMemcpyAsync(c->plan.d_items, items.data(), items.size() * sizeof(int),
                              hipMemcpyHostToDevice, c->stream));

@@ -90,7 +90,7 @@ struct SigmaPlan {
   int variant = 0;
   int RT = 16;
   int nitems = 0;
-  int units = 8192, unit_items = 0;  // a product's aux splits: units / (unit_items k)
+  int units = 8192;  // a product's aux splits: units / (nitems k)
   int npan_v = 0;
   int* d_items = nullptr;
 };
@@ -109,6 +109,8 @@ SigmaSums sigma_sums(const AbGeometry& g, Store st, int k, int nsplit);
 // Kernel variant of a restricted context and its work items (panel index << 16 | first row tile):
 // panels of adjacent column tiles of one diagonal block, row ranges of RT tiles.
 void make_sigma_plan(const Geometry& g, Store st, int nprod, SigmaPlan& plan, std::vector<int>& items);
+constexpr int UNITS_F64 = 16384;      // work units per launch of the pipelined FP64 kernel
+constexpr int F64_PIPE_MIN_NVT = 20;  // virtual 16-tiles from which FP64 sigma uses that kernel
 constexpr int BF16_WIDE_MIN_NVT = 32;  // the same for the wide-panel BF16x6 kernel
 // Largest order of the dense pencil solves on the device (the direct diagonalisation and the
 // whole-spectrum solve of the correlation energy), and the largest order solved by one

@@ -582,13 +582,12 @@ void make_sigma_plan(const Geometry& g, Store st, int nprod, SigmaPlan& plan, st
   // large virtual blocks that it tiles with full 8-tile panels (a ragged last panel idles waves
   // of its workgroup: at 26 tiles = 3 x 8 + 2 it measured no faster than the 4-tile kernel)
   const bool wide = st == Store::BF16 && nprod == 6 && g.nvt >= BF16_WIDE_MIN_NVT && g.nvt % 8 == 0;
-  plan.variant = st == Store::F64 ? 1 : (st == Store::F32 ? 4 : (wide ? 7 : 3));
-  // large FP64 blocks: the workspace of 16384 units of 32 row tiles, for the two-product form
-  const bool large = st == Store::F64 && g.nvt >= 20;
-  plan.units = large ? 16384 : 8192;
-  plan.RT = st == Store::F64 ? 16 : 32;
-  sigma_items(g, large ? 32 : plan.RT, wide ? 8 : 4, items, plan.npan_v);
-  plan.unit_items = (int)items.size();
+  // FP64: the software-pipelined kernel (k_sigma_f64.hip) for large virtual blocks; below that its
+  // units are too short to keep the pipeline full and the two-workgroup kernel is faster
+  const bool large = st == Store::F64 && g.nvt >= F64_PIPE_MIN_NVT;
+  plan.variant = st == Store::F64 ? (large ? 5 : 1) : (st == Store::F32 ? 4 : (wide ? 7 : 3));
+  plan.units = large ? UNITS_F64 : 8192;
+  plan.RT = st == Store::F64 && !large ? 16 : 32;
   sigma_items(g, plan.RT, wide ? 8 : 4, items, plan.npan_v);
   plan.nitems = (int)items.size();
 }
@@ -610,35 +609,44 @@ static hipError_t run_group(const GroupMember* m, int n, hipStream_t s) {
 }
 
 hipError_t launch_sigma_group_bf16(const GroupMember* m, int n, hipStream_t s);
+hipError_t launch_sigma_group_f64(const GroupMember* m, int n, hipStream_t s);
+hipError_t launch_sigma_f64(const Geometry& g, const SigmaPlan& plan, const SigmaLaunch& la,
+                            hipStream_t s);
 
 static hipError_t launch_sigma_group_fused(const GroupMember* m, int n, hipStream_t s) {
+  if (n == 0) return hipSuccess;
   const int variant = m[0].plan->variant;
   for (int i = 1; i < n; ++i)
     if (m[i].plan->variant != variant || m[i].la.nprod != m[0].la.nprod) return hipErrorInvalidValue;
   switch (variant) {
     case 1: return run_group<double, 8, 16, 2>(m, n, s);
+    case 5: return launch_sigma_group_f64(m, n, s);
     case 4: return run_group<float, 16, 32, 2>(m, n, s);
     default: return launch_sigma_group_bf16(m, n, s);
   }
 }
 
 // Members of the two-product form each fill the chip: one after the other, then the rest as one
-// grid.
+// grid (two in FP64, which has two kernels for the rest).
 hipError_t launch_sigma_group(const GroupMember* m, int n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (n > GROUP_MAX) return hipErrorInvalidValue;
-  GroupMember rest[GROUP_MAX];
-  int nrest = 0;
+  GroupMember rest[GROUP_MAX], large[GROUP_MAX];
+  int nrest = 0, nlarge = 0;
   for (int i = 0; i < n; ++i) {
     const SigmaLaunch& la = m[i].la;
     if (mm_plan(m[i].st, mm_geometry(*m[i].g), la.k, la.nsplit * la.k).nslot == 0) {
-      rest[nrest++] = m[i];
+      if (m[i].plan->variant == 5)
+        large[nlarge++] = m[i];
+      else
+        rest[nrest++] = m[i];
       continue;
     }
     const hipError_t e = launch_sigma(*m[i].g, m[i].st, *m[i].plan, la, s);
     if (e != hipSuccess) return e;
   }
-  return nrest ? launch_sigma_group_fused(rest, nrest, s) : hipSuccess;
+  const hipError_t e = launch_sigma_group_fused(large, nlarge, s);
+  return e == hipSuccess ? launch_sigma_group_fused(rest, nrest, s) : e;
 }
 
 hipError_t launch_sigma_bf16(const Geometry& g, const SigmaPlan& plan, const SigmaLaunch& la,
@@ -655,6 +663,7 @@ hipError_t launch_sigma(const Geometry& g, Store st, const SigmaPlan& plan, cons
     return launch_sigma_mm(st, mg, m, la.L, la.L, la.ZT, la.Sp, la.ws_slots, la.k, s);
   switch (plan.variant) {
     case 1: return run_sandwich<double, 8, 16, 2>(g, plan, la, s);
+    case 5: return launch_sigma_f64(g, plan, la, s);
     case 4: return run_sandwich<float, 16, 32, 2>(g, plan, la, s);
     default: return launch_sigma_bf16(g, plan, la, s);
   }

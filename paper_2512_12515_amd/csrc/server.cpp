@@ -254,6 +254,9 @@ void admission_loop(pprpa_server* S) {
   S->cv_work.notify_all();
 }
 
+// Solves with the same key go into one group (FP64's two kernels share one).
+int variant_key(const pprpa_ctx* c) { return (c->plan.variant == 5 ? 1 : c->plan.variant) * 8 + c->nprod; }
+
 // Grouped sigma for the solves in `grp` (all in NEED_SIGMA with their block unpacked, one kernel
 // variant).
 // Returns false if the group launch failed (its members are then failed by the caller).
@@ -386,10 +389,10 @@ void worker_loop(pprpa_server* S) {
               progressed = true;
             }
           }
-          if (r->unpacked) need[r->cls][c->plan.variant * 8 + c->nprod].push_back(r);
+          if (r->unpacked) need[r->cls][variant_key(c)].push_back(r);
         }
       } else if (sv.phase != Solver::DONE) {
-        busy_phases[r->cls][r->ctx->plan.variant * 8 + r->ctx->nprod] += 1;
+        busy_phases[r->cls][variant_key(r->ctx)] += 1;
       }
       if (sv.phase == Solver::DONE) finished.push_back(r);
     }
