@@ -186,7 +186,11 @@ typedef struct {
  * (hh). resid: [nroot] host or NULL. rep: host or NULL. Returns ENOCONV (outputs filled with
  * the last iterate) when max_iter is reached, ENONDEF if the projected pencil is not definite,
  * EUNSUPPORTED for direct without a dense build or above order 8192, EINVAL for nroot > n_pp
- * (pp) or > n_hh (hh). */
+ * (pp) or > n_hh (hh).
+ * The direct solve, the correlation energies and the NTO weights of orders up to 2048 keep the
+ * matrix on up to a workgroup per compute unit, which wait for one another. Where several processes
+ * use one device for such calls at once, or its compute units are taken otherwise, one can find them
+ * taken: it then solves in another way after 2 to 4 seconds, with the same results to rounding. */
 pprpa_status pprpa_davidson(pprpa_ctx* ctx, const pprpa_davidson_args* args, double* omega,
                             double* vecs, double* resid, pprpa_report* rep);
 

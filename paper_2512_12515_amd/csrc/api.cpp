@@ -308,6 +308,23 @@ int staging_chunk(size_t per, int naux) {
   return (int)std::max<size_t>(1, std::min<size_t>((size_t)std::max(naux, 1), cap));
 }
 
+// Whether the stream may use only a part of the device's compute units (a mask without any bit, or none to be had: no).
+bool stream_is_masked(hipStream_t s, int device) {
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1) {
+    (void)hipGetLastError();
+    return false;
+  }
+  std::vector<uint32_t> mask((cus + 31) / 32, 0);
+  if (hipExtStreamGetCUMask(s, (uint32_t)mask.size(), mask.data()) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int bits = 0;
+  for (uint32_t m : mask) bits += __builtin_popcount(m);
+  return bits > 0 && bits < cus;
+}
+
 // Stream (the caller's or a new non-blocking one), timing events and the pinned status buffer of
 // a context, on the current device.
 pprpa_status setup_runtime(pprpa_ctx* c, void* stream) {
@@ -318,6 +335,8 @@ pprpa_status setup_runtime(pprpa_ctx* c, void* stream) {
     PPRPA_HIP(hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking));
     c->own_stream = true;
   }
+  // the one-launch reduction needs its workgroups on the chip together
+  if (stream_is_masked(c->stream, c->device)) c->tridiag_polls = -1;
   PPRPA_HIP(hipEventCreate(&c->e0));
   PPRPA_HIP(hipEventCreate(&c->e1));
   c->pinned_elems = PINNED_ELEMS;

@@ -32,7 +32,8 @@
 // Every wait ends: a workgroup's stores of step k depend on its own earlier steps and on the other
 // workgroups' stores of steps before k only, the workgroups of a launch fit the chip at once (at
 // most one per compute unit), and launches of different streams are ordered one after the other
-// (launch_tridiag). Several processes on one device can still each hold a part of it and wait for
+// (launch_tridiag). A context whose stream may use only a part of the compute units does without this
+// form. Several processes on one device can still each hold a part of it and wait for
 // the rest: a poll that does not end within TRIDIAG_POLLS tries (some seconds) gives up, it raises the
 // abort flag, which every poll reads, and the host solves again by launches a step. (With no tries at
 // all every workgroup gives up at its first poll: how the tests reach that.)

@@ -82,3 +82,44 @@ def check_nto(ctx, z):
     for a, b, c in zip(one, gave_up, launches):
         assert np.array_equal(b, c)
         assert np.max(np.abs(a - b)) <= 1e-12 * max(np.abs(a).max(), 1e-300)
+
+
+def test_stream_with_a_part_of_the_compute_units():
+    """A context on a stream that may use half of the compute units reduces by launches a step, at once."""
+    import time
+
+    import torch
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL("libamdhip64.so.7")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    mask = (ctypes.c_uint32 * ((cus + 31) // 32))(*[0xFFFFFFFF] * (cus // 64))  # the first half
+    stream = ctypes.c_void_p()
+    hip.hipExtStreamCreateWithCUMask.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_uint32,
+                                                 ctypes.POINTER(ctypes.c_uint32)]
+    hip.hipStreamDestroy.argtypes = [ctypes.c_void_p]
+    rc = hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), len(mask), mask)
+    if rc != 0:
+        torch.cuda.synchronize()
+        pytest.skip(f"no stream with a compute unit mask here (HIP error {rc})")
+    nocc, nvir = 12, 32
+    eps, L = gen.orbital_energies(87, nocc, nvir), gen.lpq_full(87, nocc + nvir, 60)
+
+    def solve(ctx):
+        r = ctx.davidson(3, direct=True, vectors=True)
+        return [r["omega"], r["vecs"], np.array(list(ctx.correlation_energy().values()))]
+
+    try:
+        with P.PpRPA(eps, L, nocc, dense=True) as ctx:
+            set_polls(ctx, -1)
+            ref = solve(ctx)
+        with P.PpRPA(eps, L, nocc, dense=True, stream=stream.value) as ctx:
+            solve(ctx)
+            print("dense on a part of the compute units", flush=True)
+            t = time.perf_counter()
+            got = solve(ctx)
+            t = time.perf_counter() - t
+    finally:
+        assert hip.hipStreamDestroy(stream) == 0
+    for a, b in zip(got, ref):
+        assert np.array_equal(a, b)
+    assert t < 1.0  # (a reduction that waits in vain takes seconds)
