@@ -626,26 +626,40 @@ static hipError_t launch_sigma_group_fused(const GroupMember* m, int n, hipStrea
   }
 }
 
-// Members of the two-product form each fill the chip: one after the other, then the rest as one
-// grid (two in FP64, which has two kernels for the rest).
+// Members of the two-product form in BF16 each fill the chip (160 column tiles and more): one after the
+// other. In FP64 and FP32 a product of a few virtual tiles does not, and a served one takes several launches,
+// each with a tail: theirs go side by side (ms of sigma of the same served products one after the other /
+// side by side / in the one-kernel form: 5/20/100 FP64, 10 vectors 15.2 / 9.8 / 12.0; 13/117/457 FP64, 4 vectors
+// 176 / 136 / 145; 20/200/700 FP64, 5 vectors 401 / 376 / 450).
+// The rest as one grid (two in FP64, which has two kernels for the rest).
 hipError_t launch_sigma_group(const GroupMember* m, int n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (n > GROUP_MAX) return hipErrorInvalidValue;
   GroupMember rest[GROUP_MAX], large[GROUP_MAX];
-  int nrest = 0, nlarge = 0;
+  MmGeometry mg[GROUP_MAX];
+  MmProduct mm[GROUP_MAX];
+  int nrest = 0, nlarge = 0, nmm = 0;
   for (int i = 0; i < n; ++i) {
     const SigmaLaunch& la = m[i].la;
-    if (mm_plan(m[i].st, mm_geometry(*m[i].g), la.k, la.nsplit * la.k).nslot == 0) {
+    const MmGeometry gi = mm_geometry(*m[i].g);
+    const MmPlan plan = mm_plan(m[i].st, gi, la.k, la.nsplit * la.k);
+    if (plan.nslot == 0) {
       if (m[i].plan->variant == 5)
         large[nlarge++] = m[i];
       else
         rest[nrest++] = m[i];
       continue;
     }
+    if (m[i].st != Store::BF16) {
+      mg[nmm] = gi;
+      mm[nmm++] = MmProduct{plan, la.L, la.L, la.ZT, la.Sp, la.ws_slots, la.k};
+      continue;
+    }
     const hipError_t e = launch_sigma(*m[i].g, m[i].st, *m[i].plan, la, s);
     if (e != hipSuccess) return e;
   }
-  const hipError_t e = launch_sigma_group_fused(large, nlarge, s);
+  hipError_t e = launch_sigma_mm_group(m[0].st, mg, mm, nmm, s);
+  if (e == hipSuccess) e = launch_sigma_group_fused(large, nlarge, s);
   return e == hipSuccess ? launch_sigma_group_fused(rest, nrest, s) : e;
 }
 
@@ -660,7 +674,7 @@ hipError_t launch_sigma(const Geometry& g, Store st, const SigmaPlan& plan, cons
     return launch_sigma_bf16_mm(mg, m, la.nprod, la.L, la.plane, la.ZT, la.zplane, la.Sp, la.ws_slots,
                                 la.k, s);
   if (m.nslot > 0)
-    return launch_sigma_mm(st, mg, m, la.L, la.L, la.ZT, la.Sp, la.ws_slots, la.k, s);
+    return launch_sigma_mm(st, mg, MmProduct{m, la.L, la.L, la.ZT, la.Sp, la.ws_slots, la.k}, s);
   switch (plan.variant) {
     case 1: return run_sandwich<double, 8, 16, 2>(g, plan, la, s);
     case 5: return launch_sigma_f64(g, plan, la, s);

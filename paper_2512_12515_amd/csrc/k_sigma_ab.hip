@@ -555,7 +555,7 @@ hipError_t launch_sigma_ab(const AbGeometry& g, Store st, int nprod, const Sigma
                            int k, int nsplit, int64_t ws_slots, hipStream_t s) {
   const MmGeometry mg = mm_geometry(g);
   const MmPlan m = mm_plan(st, mg, k, nsplit * k);
-  if (m.nslot > 0) return launch_sigma_mm(st, mg, m, La, Lb, ZT, Qp, ws_slots, k, s);
+  if (m.nslot > 0) return launch_sigma_mm(st, mg, MmProduct{m, La, Lb, ZT, Qp, ws_slots, k}, s);
   AbParams p;
   p.nvta = g.nvta;
   p.ncta = g.ncta;

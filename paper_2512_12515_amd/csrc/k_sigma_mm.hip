@@ -28,7 +28,9 @@
 //   * phase 2 splits the aux index into slots, each with its own sums in registers over the whole
 //     slot (no partial sums in between), so that the units fill whole rounds of the chip; launch c
 //     runs phase 2 of part c - 1 of every slot and phase 1 of part c, whose short units fill the
-//     long ones' tail. FP32 sums are chains of one aux index (16 times the c tiles), added up in
+//     long ones' tail. Where the workspace is small (served requests) a launch takes some slots whole
+//     instead, if enough products are in it to fill the chip: the sums then stay in registers (a part of
+//     one aux index reads and writes them every 9 stages at 13/117/457). FP32 sums are chains of one aux index (16 times the c tiles), added up in
 //     FP64 in registers: 7.8e-8 relative error at 40/400/1540, against 2.3e-7 of the one-kernel form.
 // What bounds it: the matrix pipe, busy 87 % of the time at 50/500/1800 (61 % before); the direct
 // loads cost 6.7 %, the barriers 1.6 %, launch tails about 2 %. Times (us; 12-20 vectors):
@@ -198,18 +200,20 @@ template <typename T> struct Run {
   int n, mt;
 };
 
+template <typename T> constexpr int mm_lds() {  // elements of the two stage buffers
+  return 2 * KS * (AW + MW * NT * TILE);
+}
+
+// Unit idx of XCD xcd of a product's launch.
 template <typename T>
-__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
-void k_sigma_mm(MmParams p) {
+__device__ __forceinline__ void mm_unit(const MmParams& p, T* buf, const int xcd, const int idx) {
   constexpr int BT = MW * NT, BW = BT * TILE, VEC = 16 / (int)sizeof(T);
   constexpr int RA = 64 * VEC / AW;         // A rows one wave load covers
   constexpr int STAGE = KS * AW + KS * BW;  // elements per stage buffer
   constexpr unsigned SB = STAGE * sizeof(T);
   constexpr int RB = 64 * VEC / BW;         // B rows one wave load covers
   static_assert(RB >= 1 && KS % (RB * MW) == 0, "whole wave loads");
-  __shared__ __attribute__((aligned(65536))) T buf[2 * STAGE];
-
-  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+  static_assert(2 * STAGE == mm_lds<T>(), "stage buffers");
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 15, lk = lane >> 4;
   // this lane's place in an A load (row, column), in a B row and in the output columns
@@ -265,9 +269,9 @@ void k_sigma_mm(MmParams p) {
     const int items = virt ? p.items2v : p.items2 - p.items2v;
     const int u = virt ? xcd * p.per2v + idx : xcd * (p.per2 - p.per2v) + idx - p.per2v;
     const int ro = virt ? 1 : p.ro;
-    if (u >= items * p.nslot * ro) return;
-    const int slot = u / items, it = u - slot * items;
-    const int s = slot / ro, r = slot - s * ro;
+    if (u >= items * p.slots2 * ro) return;
+    const int slot = u / items, it = u - slot * items;  // of this launch
+    const int sl = slot / ro, r = slot - sl * ro, s = p.slot2 + sl;
     const int lo = mm_cut(0, p.naux, p.nslot, s), hi = mm_cut(0, p.naux, p.nslot, s + 1);
     const int Plo = mm_cut(lo, hi, ro, r), Phi = mm_cut(lo, hi, ro, r + 1);
     const int Ppart = mm_cut(lo, hi, p.nparts, p.part2);
@@ -296,9 +300,9 @@ void k_sigma_mm(MmParams p) {
     const int64_t qs = virt ? p.qstride : p.qostride;
     double* const Q = virt ? p.Q : p.Qo;
     const unsigned ldq = virt ? p.nmopb : btb * TILE;
-    const size_t q0 = (size_t)slot * p.k * qs + (size_t)(t0 * TILE) * ldq;
+    const size_t q0 = (size_t)(p.slot2 * ro + slot) * p.k * qs + (size_t)(t0 * TILE) * ldq;
     const unsigned vq = (unsigned)(okv * qs + (oct - ctile0) * TILE + cs);
-    const size_t k0 = (size_t)Pa * p.ncta * KS, kt0 = (size_t)(s * p.mc + Pa - Ppart) * p.ncta * KS;
+    const size_t k0 = (size_t)Pa * p.ncta * KS, kt0 = (size_t)(sl * p.mc + Pa - Ppart) * p.ncta * KS;
     Run<T> ld{(const char*)p.La + k0 * lda + row0 * sizeof(T), (const char*)p.Tin + kt0 * ldb,
               (Pb - Pa) * p.ncta, mt};
     const int n = ld.n;
@@ -362,7 +366,7 @@ void k_sigma_mm(MmParams p) {
   const int u = xcd * p.per1 + idx - p.per2;
   if (u >= p.units1) return;
   const int kv = u % p.k, us = u / p.k;
-  const int s = us / p.nbs, nb = us - s * p.nbs;
+  const int sl = us / p.nbs, nb = us - sl * p.nbs, s = p.slot1 + sl;
   const int lo = mm_cut(0, p.naux, p.nslot, s), hi = mm_cut(0, p.naux, p.nslot, s + 1);
   const int Ppart = mm_cut(lo, hi, p.nparts, p.part1);
   const int ntot = (mm_cut(lo, hi, p.nparts, p.part1 + 1) - Ppart) * p.nctb;
@@ -379,7 +383,7 @@ void k_sigma_mm(MmParams p) {
   const bool store = jo < ntot;
   const int oP = min(jo, ntot - 1) / p.nctb;
   const unsigned so = p.k * p.nmopb * sizeof(T);  // row stride of T, bytes
-  char* const out = (char*)p.Tout + (size_t)(s * p.mc + P0) * p.nmopa * so + (size_t)kv * p.nmopb * sizeof(T);
+  char* const out = (char*)p.Tout + (size_t)(sl * p.mc + P0) * p.nmopa * so + (size_t)kv * p.nmopb * sizeof(T);
   const unsigned vt = (unsigned)(oP - P0) * p.nmopa * so +
                       (unsigned)(((min(jo, ntot - 1) - oP * p.nctb) * TILE + cs) * sizeof(T));
   const int npan = p.npv + p.npo;
@@ -452,6 +456,38 @@ void k_sigma_mm(MmParams p) {
     });
     c0 = c0n;
   }
+}
+
+template <typename T>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
+void k_sigma_mm(MmParams p) {
+  __shared__ __attribute__((aligned(65536))) T buf[mm_lds<T>()];
+  mm_unit<T>(p, buf, blockIdx.x & 7, blockIdx.x >> 3);
+}
+
+// Grouped launch (serving): the same launch of several products in one grid, on every XCD the phase 2
+// units (the long ones) of all products first, then the phase 1 units. A unit does exactly what it does
+// in its own product's launch.
+struct MmGroup {
+  int n, b2[GROUP_MAX + 1], b1[GROUP_MAX + 1];  // first unit of product e on an XCD, by phase
+  MmParams e[GROUP_MAX];
+};
+static_assert(sizeof(MmGroup) <= 4096, "kernel arguments");
+
+template <typename T>
+__global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
+void k_sigma_mm_group(MmGroup ga) {
+  __shared__ __attribute__((aligned(65536))) T buf[mm_lds<T>()];
+  int idx = blockIdx.x >> 3, e = 0;
+  if (idx < ga.b2[ga.n]) {
+    while (idx >= ga.b2[e + 1]) ++e;
+    idx -= ga.b2[e];
+  } else {
+    idx -= ga.b2[ga.n];
+    while (idx >= ga.b1[e + 1]) ++e;
+    idx += ga.e[e].per2 - ga.b1[e];
+  }
+  mm_unit<T>(ga.e[e], buf, blockIdx.x & 7, idx);
 }
 
 }  // namespace
@@ -538,10 +574,30 @@ MmPlan mm_plan(Store st, const MmGeometry& g, int k, int slots) {
   return m;
 }
 
-template <typename T>
-static hipError_t run_mm(const MmGeometry& g, const MmPlan& m, const void* La, const void* Lb,
-                         const void* UT, void* ws, int64_t ws_slots, int k, hipStream_t s) {
-  MmParams p{};
+// Longest slot, and the matrices of T that the workspace holds.
+static int mm_len(const MmGeometry& g, const MmProduct& a) { return (g.naux + a.m.nslot - 1) / a.m.nslot; }
+static int64_t mm_room(const MmProduct& a) { return a.ws_slots - a.m.qslots; }
+
+// Parts of every slot: all of T in one buffer, or as much as two hold.
+static int mm_parts(const MmGeometry& g, const MmProduct& a) {
+  const int64_t len = mm_len(g, a), room = mm_room(a) / ((int64_t)a.k * a.m.nslot);
+  return room >= len ? 1 : (int)((len + room / 2 - 1) / (room / 2));
+}
+
+// Whole slots of a launch, half of the workspace, for which a product gives up its parts: those of under
+// MM_RUN_PART aux indices each (0: none).
+static int mm_whole_slots(const MmGeometry& g, const MmProduct& a) {
+  const int len = mm_len(g, a), parts = mm_parts(g, a);
+  if (parts == 1 || (len + parts - 1) / parts >= MM_RUN_PART) return 0;
+  return (int)(mm_room(a) / 2 / ((int64_t)len * a.k));
+}
+
+// Kernel arguments of a product, but for those of one launch (step). slots: those of a launch, whole, or 0: all, in
+// parts.
+static hipError_t mm_params(Store st, const MmGeometry& g, const MmProduct& a, int slots, MmParams& p) {
+  const MmPlan& m = a.m;
+  const int k = a.k;
+  p = MmParams{};
   p.nvta = g.nvta;
   p.ncta = g.ncta;
   p.nvtb = g.nvtb;
@@ -557,46 +613,100 @@ static hipError_t run_mm(const MmGeometry& g, const MmPlan& m, const void* La, c
   p.nslot = m.nslot;
   p.ro = m.ro;
   p.naux = g.naux;
-  p.La = La;
-  p.Lb = Lb;
-  p.UT = UT;
+  p.La = a.La;
+  p.Lb = a.Lb;
+  p.UT = a.UT;
   p.ustride = (int64_t)p.nmopb * p.nmopa;
   p.lbstride = (int64_t)p.nmopb * p.nmopb;
   p.qstride = (int64_t)p.nmopa * p.nmopb;
   p.qostride = (int64_t)(g.ncta - g.nvta) * (g.nctb - g.nvtb) * TILE * TILE;
-  p.Q = (double*)ws;
+  p.Q = (double*)a.ws;
   p.Qo = p.Q + (int64_t)m.nslot * k * p.qstride;
-  // parts of T: all of it in one buffer, or as much as two hold
-  const int len = (g.naux + m.nslot - 1) / m.nslot;  // longest slot
-  const int64_t room = (ws_slots - m.qslots) / ((int64_t)k * m.nslot);
+  const int len = mm_len(g, a);
+  const int64_t room = mm_room(a) / ((int64_t)k * m.nslot);
   if (room < 2 && room < len) return hipErrorInvalidValue;
-  if (room >= len)
-    p.nparts = 1;
-  else
-    p.nparts = (int)((len + room / 2 - 1) / (room / 2));
+  p.nrun = slots > 0 ? slots : m.nslot;
+  p.nparts = slots > 0 ? 1 : mm_parts(g, a);
   p.mc = (len + p.nparts - 1) / p.nparts;
   p.nbs = (p.mc * g.nctb + MM_BT - 1) / MM_BT;
-  T* const t0 = (T*)ws + m.qslots * p.qstride;
-  const int64_t tpart = (int64_t)m.nslot * p.mc * k * p.qstride;
-  for (int c = 0; c <= p.nparts; ++c) {  // launch c: phase 2 of part c - 1 and phase 1 of part c
-    p.part1 = c;
-    p.part2 = c - 1;
-    p.Tout = t0 + (c & 1) * tpart;
-    p.Tin = t0 + ((c + 1) & 1) * tpart;
-    p.units1 = c < p.nparts ? k * m.nslot * p.nbs : 0;
-    p.per1 = (p.units1 + 7) / 8;
-    p.per2v = c > 0 ? (m.items2v * m.nslot + 7) / 8 : 0;
-    p.per2 = c > 0 ? p.per2v + ((m.items2 - m.items2v) * m.nslot * m.ro + 7) / 8 : 0;
-    hipLaunchKernelGGL((k_sigma_mm<T>), dim3(8 * (p.per1 + p.per2)), dim3(MW * 64), 0, s, p);
+  const int64_t size = st == Store::F64 ? 8 : 4;
+  p.T0 = (char*)a.ws + m.qslots * p.qstride * size;
+  p.tpart = (int64_t)p.nrun * p.mc * k * p.qstride * size;
+  return hipSuccess;
+}
+
+// Launch c of a product: phase 2 of part c - 1 (or of run c - 1 of the slots) and phase 1 of part c.
+static int mm_launches(const MmParams& p) {
+  return (p.nparts > 1 ? p.nparts : (p.nslot + p.nrun - 1) / p.nrun) + 1;
+}
+static void mm_step(MmParams& p, int c) {
+  p.part1 = p.nparts > 1 ? c : 0;
+  p.part2 = p.nparts > 1 ? c - 1 : 0;
+  p.slot1 = p.nparts > 1 ? 0 : c * p.nrun;
+  p.slot2 = p.nparts > 1 ? 0 : (c - 1) * p.nrun;
+  p.slots1 = c + 1 < mm_launches(p) ? std::min(p.nrun, p.nslot - p.slot1) : 0;
+  p.slots2 = c > 0 ? std::min(p.nrun, p.nslot - p.slot2) : 0;
+  p.Tout = p.T0 + (c & 1) * p.tpart;
+  p.Tin = p.T0 + ((c + 1) & 1) * p.tpart;
+  p.units1 = p.k * p.slots1 * p.nbs;
+  p.per1 = (p.units1 + 7) / 8;
+  p.per2v = (p.items2v * p.slots2 + 7) / 8;
+  p.per2 = p.per2v + ((p.items2 - p.items2v) * p.slots2 * p.ro + 7) / 8;
+}
+
+hipError_t launch_sigma_mm(Store st, const MmGeometry& g, const MmProduct& a, hipStream_t s) {
+  MmParams p;
+  const hipError_t e = mm_params(st, g, a, 0, p);
+  if (e != hipSuccess) return e;
+  for (int c = 0; c < mm_launches(p); ++c) {
+    mm_step(p, c);
+    const dim3 grid(8 * (p.per1 + p.per2)), wg(MW * 64);
+    if (st == Store::F64)
+      hipLaunchKernelGGL(k_sigma_mm<double>, grid, wg, 0, s, p);
+    else
+      hipLaunchKernelGGL(k_sigma_mm<float>, grid, wg, 0, s, p);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_sigma_mm(Store st, const MmGeometry& g, const MmPlan& m, const void* La,
-                           const void* Lb, const void* UT, void* ws, int64_t ws_slots, int k,
-                           hipStream_t s) {
-  if (st == Store::F64) return run_mm<double>(g, m, La, Lb, UT, ws, ws_slots, k, s);
-  return run_mm<float>(g, m, La, Lb, UT, ws, ws_slots, k, s);
+hipError_t launch_sigma_mm_group(Store st, const MmGeometry* g, const MmProduct* a, int n,
+                                 hipStream_t s) {
+  if (n < 1 || n > GROUP_MAX) return n == 0 ? hipSuccess : hipErrorInvalidValue;
+  if (n == 1) return launch_sigma_mm(st, g[0], a[0], s);
+  for (int i = 0; i < n; ++i)
+    if (mm_room(a[i]) < std::min(2, mm_len(g[i], a[i])) * (int64_t)a[i].k * a[i].m.nslot)
+      return hipErrorInvalidValue;
+  // runs of whole slots where they make enough phase 2 units a launch (with the phase 1 units beside them,
+  // about as much work). Sigma time of 448 served products at 13/117/457 in FP32, 8 vectors, ms, for at least 256 /
+  // 96 / 32 units: 151 / 132 / 133; 512 with 4 vectors, 32 solves in flight 110 / 106 / 108, 4 in flight
+  // 113 / 117 / 133.
+  int64_t units = 0;
+  for (int i = 0; i < n; ++i) units += (int64_t)a[i].m.items2v * mm_whole_slots(g[i], a[i]);
+  MmParams p[GROUP_MAX];
+  int most = 0;
+  for (int i = 0; i < n; ++i) {
+    const hipError_t e = mm_params(st, g[i], a[i], units >= 96 ? mm_whole_slots(g[i], a[i]) : 0, p[i]);
+    if (e != hipSuccess) return e;
+    most = std::max(most, mm_launches(p[i]));
+  }
+  for (int c = 0; c < most; ++c) {
+    MmGroup ga;
+    ga.n = 0;
+    ga.b2[0] = ga.b1[0] = 0;
+    for (int i = 0; i < n; ++i) {
+      if (c >= mm_launches(p[i])) continue;
+      mm_step(p[i], c);
+      ga.b2[ga.n + 1] = ga.b2[ga.n] + p[i].per2;
+      ga.b1[ga.n + 1] = ga.b1[ga.n] + p[i].per1;
+      ga.e[ga.n++] = p[i];
+    }
+    const dim3 grid(8 * (ga.b2[ga.n] + ga.b1[ga.n])), wg(MW * 64);
+    if (st == Store::F64)
+      hipLaunchKernelGGL(k_sigma_mm_group<double>, grid, wg, 0, s, ga);
+    else
+      hipLaunchKernelGGL(k_sigma_mm_group<float>, grid, wg, 0, s, ga);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace pprpa

@@ -20,9 +20,10 @@
 //   different kernel variants (sigma precision, BF16x6 kernel by size) cannot share a grid; the
 //   variant whose waiting block has waited longest goes next, so no request is overtaken by more
 //   than one launch per other variant of its class. Members whose product runs as two matrix
-//   products, each enough for the chip, go one after the other ahead of the rest's grid. A member's
-//   work units are those of a launch of its own (same decomposition, same partial-sum buffer), so
-//   its results do not depend on the mix it was served in.
+//   products go ahead of the rest's grid, in FP64 and FP32 side by side in grids of their own, in BF16,
+//   where each is enough for the chip, one after the other. A member's work units are those of a launch
+//   of its own (same decomposition, same partial-sum buffer), so its results do not depend on the mix it
+//   was served in.
 // * Finished solves copy out their roots, release their reservation and slot, and wake the
 //   admission thread.
 #include <algorithm>

@@ -10,6 +10,11 @@ namespace pprpa {
 constexpr int MM_MT = 8;      // row tiles per panel
 constexpr int MM_BT = 8;      // column tiles per unit
 constexpr int BF_MT = 16;     // row tiles per panel of the BF16 form
+// Aux indices of a part below which a product in a group takes runs of whole slots instead (requests/s served,
+// parts -> runs: 13/117/457 FP64, 7 vectors, parts of one 226 -> 254; 15/150/550 FP32, 5 vectors, parts of two
+// 244 -> 256, FP64, 8 vectors, parts of four 126.7 -> 126.6; 20/200/700 FP64, 5 vectors, parts of four
+// 59.6 -> 56.6).
+constexpr int MM_RUN_PART = 4;
 constexpr int MM_RO = 8;      // most slots of the occupied block per slot of the virtual one
 // Fewest column tiles of a block of vectors (k x virtual tiles) from which this form runs. us, the
 // one-kernel form -> this one: FP64 5/20/100 8 vectors (16 tiles) 66 -> 57, 13/117/457 1 vector (8)
@@ -81,13 +86,16 @@ struct MmParams {
   int nvta, ncta, nvtb, nctb, nmopa, nmopb, k, tri;
   int npv, npo, items2v, items2, nslot, ro, naux;
   int nparts, part1, part2;  // parts of every slot's aux indices: this launch's phase 1 and phase 2
+  int nrun, slot1, slots1, slot2, slots2;  // slots of a launch, at most; this one's first and number
   int mc, nbs;               // most aux indices of a slot's part, their column blocks
   int units1, per1, per2v, per2;
   const void* La;    // [naux][nmopa][nmopa]
   const void* Lb;    // [naux][nmopb][nmopb]
   const void* UT;    // [k][nmopb][nmopa]
-  const void* Tin;   // [nslot][mc][nmopa][k][nmopb]
+  const void* Tin;   // [slots2][mc][nmopa][k][nmopb]
   void* Tout;
+  char* T0;          // the buffers of T, tpart bytes each
+  int64_t tpart;
   double* Q;         // [nslot][k][nmopa][nmopb], the virtual block
   double* Qo;        // [nslot ro][k][nopa][nopb], the occupied block
   int64_t ustride, lbstride, qstride, qostride;
@@ -97,11 +105,19 @@ MmGeometry mm_geometry(const Geometry& g);
 MmGeometry mm_geometry(const AbGeometry& g);
 // slots: the smallest workspace in units of one nmopa x nmopb matrix of the sigma precision.
 MmPlan mm_plan(Store st, const MmGeometry& g, int k, int slots);
-// ws: Q, Qo, then T, ws_slots units (at least the plan's slots).
-hipError_t launch_sigma_mm(Store st, const MmGeometry& g, const MmPlan& m, const void* La,
-                           const void* Lb, const void* UT, void* ws, int64_t ws_slots, int k,
-                           hipStream_t s);
-// The same for BF16 planes of L (plane elements apart) and U (row-major, zplane apart), restricted.
+// One product of k vectors. ws: Q, Qo, then T, ws_slots units (at least the plan's slots).
+struct MmProduct {
+  MmPlan m;
+  const void *La, *Lb, *UT;
+  void* ws;
+  int64_t ws_slots;
+  int k;
+};
+hipError_t launch_sigma_mm(Store st, const MmGeometry& g, const MmProduct& a, hipStream_t s);
+// Up to GROUP_MAX products of one precision side by side, each bit for bit as by itself.
+hipError_t launch_sigma_mm_group(Store st, const MmGeometry* g, const MmProduct* a, int n,
+                                 hipStream_t s);
+// One product for BF16 planes of L (plane elements apart) and U (row-major, zplane apart), restricted.
 hipError_t launch_sigma_bf16_mm(const MmGeometry& g, const MmPlan& m, int nprod, const void* L,
                                 size_t plane, const void* U, size_t zplane, void* ws,
                                 int64_t ws_slots, int k, hipStream_t s);
