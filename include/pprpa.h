@@ -308,7 +308,7 @@ pprpa_status pprpa_solve_stats(pprpa_solve* solve, pprpa_kernel_stats* out, int3
  * "Implementation Details"); a server keeps many solves resident and overlaps them: requests
  * are admitted in arrival order when their device footprint (staged integrals, sigma buffers,
  * Davidson workspace; computed exactly at submit) fits in the server's HBM arena and one of
- * max_inflight slots is free; every in-flight solve advances independently on its own stream,
+ * max_inflight slots is free (more sigma workspace while a quarter of the arena at most is held); every in-flight solve advances independently on its own stream,
  * and the sigma products of all solves that need one at the same time run as one grouped grid.
  * A request's arithmetic is the same as pprpa_build + pprpa_davidson with the same arguments
  * (same kernels and decomposition), so its roots do not depend on what it was served with.
@@ -329,7 +329,7 @@ typedef struct {
   double t_submit;      /* seconds on the server's steady clock (0 = creation)               */
   double t_admit;       /* reservation taken, build started                                  */
   double t_done;        /* roots copied out, memory released                                 */
-  uint64_t footprint;   /* device bytes reserved for the request                             */
+  uint64_t footprint;   /* device bytes the request needs                                     */
   char message[256];    /* error text when status != OK                                     */
 } pprpa_request_info;
 

@@ -352,6 +352,7 @@ pprpa_status setup_runtime(pprpa_ctx* c, void* stream) {
 // the least does when the rest is not free, and a later allocation of the context's that is refused gets
 // the rest. A dense context (least), built for the direct solve, does without.
 pprpa_status alloc_sums(pprpa_ctx* c, const MmGeometry& mg, size_t slots, size_t bytes, bool least) {
+  if (c->slab) slots += c->slab->more / bytes;
   c->sp_slots = c->sp_least = (int64_t)slots;
   c->sp_bytes = bytes;
   if (!c->slab && !least && slots * bytes > MM_WORKSPACE_MIN && c->device >= 0 && c->device < GATE_DEVICES &&
@@ -735,7 +736,8 @@ pprpa_status check_build_args(const pprpa_build_args* a) {
 // Every device allocation build_impl makes (plus the Davidson workspace), each rounded up to the
 // 256-byte granule of the slab allocator. Kept in step with build_impl and get_ws: a served
 // build whose allocations outrun this figure fails with ENOMEM instead of overrunning its slab.
-size_t context_footprint(const pprpa_build_args* a, const pprpa_davidson_args* d) {
+size_t context_footprint(const pprpa_build_args* a, const pprpa_davidson_args* d, size_t* more) {
+  *more = 0;
   Geometry g;
   if (check_build_args(a) != PPRPA_OK || geometry_of(a, &g) != PPRPA_OK) return 0;
   auto al = [](size_t b) { return (std::max<size_t>(b, 1) + 255) / 256 * 256; };
@@ -768,6 +770,9 @@ size_t context_footprint(const pprpa_build_args* a, const pprpa_davidson_args* d
   for (int kk = 1; kk <= kcap; ++kk)
     sp_max = std::max(sp_max, (size_t)nsplit_of(plan, g.naux, kk) * kk);
   b += al(sp_max * zz * (st == Store::F64 ? 8 : 4));  // partial sums
+  const size_t widest = mm_more(st, mm_geometry(g), kcap, nsplit_of(plan, g.naux, kcap) * kcap);
+  *more = al(std::min(widest * zz * (st == Store::F64 ? 8 : 4), MM_WORKSPACE));
+  if (widest == 0) *more = 0;
   b += 2 * al((size_t)kcap * g.n * sizeof(double));   // host-vector staging
   if (a->dense) b += al((size_t)g.n * g.n * sizeof(double));
   if (d) {

@@ -82,7 +82,8 @@ pprpa_status harvest_timing(pprpa_ctx* c);
 // footprint of a context plus one Davidson solve; build into a slab with a caller-owned pinned
 // buffer (pinned_elems doubles) and stream; release.
 pprpa_status check_build_args(const pprpa_build_args* a);
-size_t context_footprint(const pprpa_build_args* a, const pprpa_davidson_args* d);
+// more: sigma workspace beyond it that its products would use (0: none).
+size_t context_footprint(const pprpa_build_args* a, const pprpa_davidson_args* d, size_t* more);
 pprpa_status build_context(const pprpa_build_args* a, Slab* slab, double* pinned,
                            pprpa_ctx** out);
 void free_context(pprpa_ctx* c);

@@ -66,6 +66,7 @@ struct AbGeometry;
 struct Slab {
   char* base = nullptr;
   size_t size = 0, top = 0;
+  size_t more = 0;  // of size, for more sigma workspace than the least
 };
 
 // Sigma precision and storage type.

@@ -574,6 +574,14 @@ MmPlan mm_plan(Store st, const MmGeometry& g, int k, int slots) {
   return m;
 }
 
+size_t mm_more(Store st, const MmGeometry& g, int k, int slots) {
+  const MmPlan m = mm_plan(st, g, k, slots);
+  if (m.nslot == 0) return 0;
+  const int64_t len = (g.naux + m.nslot - 1) / m.nslot;
+  const int64_t t = std::min<int64_t>(len, 2 * MM_PART) * m.nslot * k * (st == Store::BF16 ? 3 : 2) / 2;
+  return (size_t)std::max<int64_t>(0, m.qslots + t - slots);
+}
+
 // Longest slot, and the matrices of T that the workspace holds.
 static int mm_len(const MmGeometry& g, const MmProduct& a) { return (g.naux + a.m.nslot - 1) / a.m.nslot; }
 static int64_t mm_room(const MmProduct& a) { return a.ws_slots - a.m.qslots; }

@@ -1,10 +1,11 @@
 // Serving loop: many independent ppRPA solves on one device (continuous batching).
 //
 // * Admission (admission thread): requests are taken in arrival order; each needs one contiguous
-//   reservation of its exact device footprint (staged integrals, sigma buffers, Davidson
+//   reservation of its device footprint (staged integrals, sigma buffers, Davidson
 //   workspace) inside the server's HBM arena, and a free slot (stream + pinned status buffer).
 //   A request that does not fit waits until finished requests release memory; one larger than
-//   the whole arena fails with ENOMEM. The build and the initial subspace run on the slot's
+//   the whole arena fails with ENOMEM. As long as three quarters of the arena stay free, a request
+//   gets what more workspace its sigma products can use (fewer, longer parts). The build and the initial subspace run on the slot's
 //   stream; after that the caller's input buffers are no longer read.
 // * Progress (worker thread): every in-flight solve is a Davidson phase machine. Each pass the
 //   worker advances every solve whose stream has drained. A solve that needs a sigma product has
@@ -96,7 +97,7 @@ struct Request {
   uint64_t ticket = 0;
   pprpa_build_args b{};
   pprpa_davidson_args d{};
-  size_t footprint = 0;
+  size_t footprint = 0, more = 0;  // what it needs, and what its sigma products would use beyond that
   int state = 0;  // 0 queued, 1 running, 2 done
   double t_submit = 0, t_admit = 0, t_done = 0;
   int slot = -1;
@@ -124,6 +125,7 @@ struct TimedGroup {
 
 constexpr int NCLS = 2;
 constexpr double LARGE_FLOPS = 1e10;  // flops of one single-vector sigma from which a solve is large
+constexpr size_t MORE_SHARE = 4;      // share of the arena up to which requests get more sigma workspace
 constexpr double HOLD_US = 300.0;     // longest hold of a small-class launch for more members
 
 }  // namespace
@@ -177,7 +179,7 @@ void release_resources(pprpa_server* S, Request* r) {
     r->slot = -1;
   }
   if (r->slab.base) {
-    S->arena.release(r->off, r->footprint);
+    S->arena.release(r->off, r->slab.size);
     r->slab = Slab{};
     S->st.reserved = S->arena.used();
   }
@@ -200,8 +202,14 @@ void admission_loop(pprpa_server* S) {
       finish_request(S, r, PPRPA_ENOMEM, buf);
       continue;
     }
-    size_t off = 0;
-    if (!S->arena.alloc(r->footprint, &off)) {
+    // more sigma workspace as long as most of the arena stays free (it is for others first)
+    size_t off = 0, more = r->more;
+    if (more == 0 || S->arena.used() + r->footprint + more > S->arena.size() / MORE_SHARE ||
+        !S->arena.alloc(r->footprint + more, &off)) {
+      more = 0;
+      off = S->arena.size();
+    }
+    if (off == S->arena.size() && !S->arena.alloc(r->footprint, &off)) {
       S->cv_admit.wait(lk);  // woken when a finished request releases memory (or on stop)
       continue;
     }
@@ -209,7 +217,8 @@ void admission_loop(pprpa_server* S) {
     S->st.queued = (int64_t)S->queue.size();
     r->off = off;
     r->slab.base = S->base + off;
-    r->slab.size = r->footprint;
+    r->slab.size = r->footprint + more;
+    r->slab.more = more;
     r->slab.top = 0;
     r->slot = S->free_slots.back();
     S->free_slots.pop_back();
@@ -594,7 +603,7 @@ pprpa_status pprpa_server_submit(pprpa_server* S, const pprpa_build_args* b,
   const int blk = d->block > 0 ? d->block : d->nroot;
   r->b.max_block = std::min(64, std::max(1, std::max(blk, d->nroot)));
   r->d = *d;
-  r->footprint = context_footprint(&r->b, &r->d);
+  r->footprint = context_footprint(&r->b, &r->d, &r->more);
   if (r->footprint == 0) {
     if (std::string(pprpa_last_error()).empty()) set_error("invalid request");
     return PPRPA_EINVAL;

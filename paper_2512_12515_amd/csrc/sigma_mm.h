@@ -101,6 +101,13 @@ struct MmParams {
   int64_t ustride, lbstride, qstride, qostride;
 };
 
+// Workspace beyond `slots` matrices that a product of k vectors uses to advantage, in matrices: that of parts of
+// MM_PART aux indices. A served request gets it while the arena is mostly free (requests/s, least -> more
+// workspace, the one-kernel form in brackets; 13/117/457, 4 roots, 32 solves in flight: FP64 322 -> 345 (311),
+// FP32 389 -> 457 (403); 4 in flight: 239 -> 277 (254), 289 -> 347 (318)).
+constexpr int MM_PART = 8;
+size_t mm_more(Store st, const MmGeometry& g, int k, int slots);
+
 MmGeometry mm_geometry(const Geometry& g);
 MmGeometry mm_geometry(const AbGeometry& g);
 // slots: the smallest workspace in units of one nmopa x nmopb matrix of the sigma precision.

@@ -34,3 +34,29 @@ def test_each_as_by_itself(prec, sizes, count, slots):
             r = srv.wait(t, timeout=60.0)
             assert r["status"] == P.binding.OK, r["message"]
             assert np.array_equal(r["omega"], own[i % len(problems)]), i
+
+
+def test_more_workspace_while_the_arena_is_free():
+    """A request has the same result with the workspace of a roomy arena, of one that has room for the
+    least only, and among many, of which the first have more; the arena's account ends at zero."""
+    nocc, nvir, naux, nroot = 13, 117, 457, 5
+    eps, L = gen.orbital_energies(97, nocc, nvir), 0.3 * gen.lpq_full(97, nocc + nvir, naux)
+    with P.PpRPA(eps, L, nocc) as ctx:
+        own = ctx.davidson(nroot, block=nroot, tol=1e-4)["omega"]
+    held = {}
+    footprint = 0
+    for name, budget, count, slots in (("roomy", 16 << 30, 1, 1), ("least", None, 1, 1), ("many", None, 12, 12)):
+        budget = budget or (footprint + (1 << 20) if name == "least" else 16 * footprint)
+        print("served workspace", name, budget, flush=True)
+        with P.Server(budget, slots) as srv:
+            tickets = [srv.submit(eps, L, nocc, nroot, block=nroot, tol=1e-4) for _ in range(count)]
+            for t in tickets:
+                r = srv.wait(t, timeout=60.0)
+                assert r["status"] == P.binding.OK, r["message"]
+                assert np.array_equal(r["omega"], own)
+                footprint = r["footprint"]
+            st = srv.stats()
+        assert st["reserved"] == 0 and st["peak_reserved"] <= budget
+        held[name] = st["peak_reserved"]
+    assert held["least"] == footprint and held["roomy"] > footprint
+    assert held["many"] <= 12 * footprint + 16 * footprint // 4
