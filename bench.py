@@ -69,7 +69,7 @@ def sigma_kernel_name(prec, nv):
     else:
         nprod = 6 if prec == "bf16x6" else 3
         k = "k_sandwich_bf16w" if nprod == 6 and t32 >= 32 and t32 % 8 == 0 else "k_sandwich_bf16<%d>" % nprod
-        if t32 >= 13 and t32 >= 0.8 * (-(-t32 // 8) * 8):
+        if t32 >= 13:
             k = "k_sigma_bf16_mm<%d> (two products; %s for blocks of under 160 column tiles)" % (nprod, k)
     return k + ": density-fitted sigma contraction"
 

@@ -534,7 +534,6 @@ MmPlan mm_plan(Store st, const MmGeometry& g, int k, int slots) {
   const int tiles = k * g.nvtb, wgs = bf ? 256 : 512;  // workgroups the chip holds
   if (tiles < (st == Store::F64 ? MM_MIN_TILES_F64 : (bf ? BF_MIN_TILES : MM_MIN_TILES_F32))) return m;
   const int ota = g.ncta - g.nvta, otb = g.nctb - g.nvtb;
-  if (bf && g.nvta < BF_MIN_FILL * ((g.nvta + 7) / 8 * 8)) return m;
   const int mt = bf ? BF_MT : MT;
   m.npv = (g.nvta + mt - 1) / mt;
   m.npo = (ota + mt - 1) / mt;

@@ -22,15 +22,13 @@ constexpr int MM_RO = 8;      // most slots of the occupied block per slot of th
 // 8/80/300 4 vectors (20) 143 -> 98.
 constexpr int MM_MIN_TILES_F64 = 16;
 constexpr int MM_MIN_TILES_F32 = 18;
-// BF16: fewest column tiles and virtual tiles, and the least share of their rows of four pairs that
-// the virtual tiles fill. us, the one-kernel form -> this one, six / three products: 20/200/700 20 vectors
-// (280 tiles) 4543 -> 4126 / 3060 -> 2737, 10 (140) 2302 -> 2361 / 1586 -> 1438; 40/400/1540 12 (312,
-// 13 pairs in 4 rows) 33.2e3 -> 29.9e3 / 20.1e3 -> 16.5e3, 2 (52) 5702 -> 5547 / 3426
-// -> 3658; 50/500/1800 20 (640) 116e3 -> 82e3 / 65.8e3 -> 46.3e3; 13/117/457 20 (8 virtual tiles) 814 ->
-// 1092 / 636 -> 722.
+// BF16: fewest column tiles and virtual tiles. us, the one-kernel form -> this one, six / three products:
+// 20/200/700 20 vectors (280 tiles) 4543 -> 4126 / 3060 -> 2737, 10 (140) 2302 -> 2361 / 1586 -> 1438;
+// 20/288/300 20 (360) 4160 -> 3630 / 2658 -> 2150; 40/400/1540 12 (312) 33.2e3 -> 29.9e3 / 20.1e3 -> 16.5e3,
+// 2 (52) 5702 -> 5547 / 3426 -> 3658; 50/500/1800 20 (640) 116e3 -> 82e3 / 65.8e3 -> 46.3e3; 13/117/457 20
+// (8 virtual tiles) 814 -> 1092 / 636 -> 722.
 constexpr int BF_MIN_TILES = 160;
 constexpr int BF_MIN_NVT = 13;
-constexpr double BF_MIN_FILL = 0.8;
 // Fewest aux indices: below, the one-kernel form has a split for every aux index whatever the block
 // width, and a vector's sigma does not depend on the block around it; that stays so.
 constexpr int MM_MIN_NAUX = 96;
