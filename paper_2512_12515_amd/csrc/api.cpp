@@ -1108,10 +1108,17 @@ static pprpa_status nto_ab(pprpa_ctx* c, int k, const double* z, int on_device, 
   const size_t dov = (size_t)k * ((size_t)noa * noa + (size_t)nob * nob);
   const size_t lv = (size_t)k * nva, lo = (size_t)k * noa;
   // z (when on the host), Gx, Gy, Dv, Do, lam_p, lam_h, workspace, flags
-  const size_t wl = nto_work(k, nva, noa);
-  const size_t total = (on_device ? 0 : zv) + gv + go + dv + dov + lv + lo + wl + 1;
+  size_t wl = nto_work(k, nva, noa);
+  const size_t total = (on_device ? 0 : zv) + gv + go + dv + dov + lv + lo + 1;
   double* buf = nullptr;
-  hipError_t e = malloc_giving_back(c, (void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
+  hipError_t e = malloc_giving_back(c, (void**)&buf, (total + wl) * sizeof(double));
+  int first = c->tridiag_polls;
+  if (e == hipErrorOutOfMemory && wl > 0) {  // without the one-launch reductions and their workspace
+    (void)hipGetLastError();
+    wl = 0;
+    first = -1;
+    e = hipMalloc((void**)&buf, total * sizeof(double));
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     set_error("NTO workspace of %zu bytes: %s", total * sizeof(double), hipGetErrorString(e));
@@ -1136,7 +1143,7 @@ static pprpa_status nto_ab(pprpa_ctx* c, int k, const double* z, int on_device, 
   if (!on_device) le = hipMemcpyAsync((void*)dz, z, zv * sizeof(double), hipMemcpyHostToDevice, s);
   const bool sv = nto_spectra(nva), so = nto_spectra(noa);
   int* hl = (int*)c->pinned;
-  for (int polls : {c->tridiag_polls, -1}) {
+  for (int polls : {first, -1}) {
     if (le != hipSuccess) break;
     hl[0] = hl[1] = 0;
     le = launch_nto_ab(dz, g.n, k, nva, nvb, noa, nob, Gx, Gy, Dv, Do, lp, lh, wk, lost, polls, s);
@@ -1181,10 +1188,17 @@ pprpa_status pprpa_nto(pprpa_ctx* c, int32_t k, const double* z, int32_t on_devi
   const size_t zv = (size_t)k * g.n, mv = (size_t)k * g.nv * g.nv, mo = (size_t)k * g.no * g.no;
   const size_t lv = (size_t)k * g.nv, lo = (size_t)k * g.no;
   // z (when on the host), X, Y, Gx, Gy, Dv, Do, lam_p, lam_h, workspace, flags
-  const size_t wl = nto_work(k, g.nv, g.no);
-  const size_t total = (on_device ? 0 : zv) + 3 * mv + 3 * mo + lv + lo + wl + 1;
+  size_t wl = nto_work(k, g.nv, g.no);
+  const size_t total = (on_device ? 0 : zv) + 3 * mv + 3 * mo + lv + lo + 1;
   double* buf = nullptr;
-  hipError_t e = malloc_giving_back(c, (void**)&buf, std::max<size_t>(total, 1) * sizeof(double));
+  hipError_t e = malloc_giving_back(c, (void**)&buf, (total + wl) * sizeof(double));
+  int first = c->tridiag_polls;
+  if (e == hipErrorOutOfMemory && wl > 0) {  // without the one-launch reductions and their workspace
+    (void)hipGetLastError();
+    wl = 0;
+    first = -1;
+    e = hipMalloc((void**)&buf, total * sizeof(double));
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     set_error("NTO workspace of %zu bytes: %s", total * sizeof(double), hipGetErrorString(e));
@@ -1211,7 +1225,7 @@ pprpa_status pprpa_nto(pprpa_ctx* c, int32_t k, const double* z, int32_t on_devi
   if (!on_device) le = hipMemcpyAsync((void*)dz, z, zv * sizeof(double), hipMemcpyHostToDevice, s);
   const bool sv = nto_spectra(g.nv), so = nto_spectra(g.no);
   int* hl = (int*)c->pinned;
-  for (int polls : {c->tridiag_polls, -1}) {
+  for (int polls : {first, -1}) {
     if (le != hipSuccess) break;
     hl[0] = hl[1] = 0;
     le = launch_nto(dz, g.n, k, g, c->ptab, X, Y, Gx, Gy, Dv, Do, lp, lh, wk, lost, polls, s);

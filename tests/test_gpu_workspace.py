@@ -96,3 +96,25 @@ def test_refused_solver_workspace_gets_the_rest(prec):
         del fill
         torch.cuda.empty_cache()
     assert np.array_equal(before, ref) and np.array_equal(after, ref)
+
+
+def test_nto_weights_with_little_memory():
+    """The workspace of the one-launch reductions (130 MB here) is done without where it does not fit."""
+    import torch
+    nocc, nvir, k = 20, 400, 64
+    eps, L = gen.orbital_energies(7, nocc, nvir), gen.lpq_full(7, nocc + nvir, 4)
+    with P.PpRPA(eps, L, nocc, max_block=1) as ctx:
+        z = gen.random_vectors(8, k, ctx.n)
+        ref = ctx.nto(z)
+        torch.cuda.empty_cache()
+        fill = []
+        while free_memory() > 400 * MB and len(fill) < 8:
+            fill.append(torch.empty(free_memory() - 350 * MB, dtype=torch.uint8, device="cuda:0"))
+        left = free_memory()
+        print("filled, free MB", left // MB, flush=True)
+        assert left <= 400 * MB
+        got = ctx.nto(z)
+        del fill
+        torch.cuda.empty_cache()
+    for key in ref:
+        assert np.max(np.abs(got[key] - ref[key])) <= 1e-12 * np.abs(ref[key]).max(), key
