@@ -464,12 +464,10 @@ __global__ __launch_bounds__(256) void k_mw_bisect(const double* __restrict__ t2
     }
     if (!done) {
       const double nlo = fmax(lo, xl), nhi = fmin(hi, xh);
-      if (nlo > nhi || (nlo == lo && nhi == hi)) {
-        done = true;
-      } else {
-        lo = nlo;
-        hi = nhi;
-      }
+      // (counts out of order lie within their rounding of the eigenvalue: it is between the two points)
+      done = nlo >= nhi || (nlo == lo && nhi == hi);
+      lo = fmin(nlo, nhi);
+      hi = fmax(nlo, nhi);
     }
   }
   const double mid = 0.5 * (lo + hi);
@@ -556,9 +554,12 @@ __global__ __launch_bounds__(256) void k_mw_select(const double* __restrict__ t2
     }
     const double nlo = fmax(lo, wg_max(xl, red));
     const double nhi = fmin(hi, wg_min(xh, red));
-    if (nlo > nhi || (nlo == lo && nhi == hi)) break;
-    lo = nlo;
-    hi = nhi;
+    // (counts out of order lie within their rounding of the eigenvalue: it is between the two points, and
+    // the bracket before, up to 257 times as wide, is off by as much)
+    const bool last = nlo >= nhi || (nlo == lo && nhi == hi);
+    lo = fmin(nlo, nhi);
+    hi = fmax(nlo, nhi);
+    if (last) break;
   }
   if (t == 0) lam[j] = 0.5 * (lo + hi);
 }
