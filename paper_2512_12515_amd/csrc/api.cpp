@@ -355,12 +355,15 @@ pprpa_status alloc_sums(pprpa_ctx* c, const MmGeometry& mg, size_t slots, size_t
   if (c->slab) slots += c->slab->more / bytes;
   c->sp_slots = c->sp_least = (int64_t)slots;
   c->sp_bytes = bytes;
-  if (!c->slab && !least && slots * bytes > MM_WORKSPACE_MIN && c->device >= 0 && c->device < GATE_DEVICES &&
+  if (!c->slab && !least && c->device >= 0 && c->device < GATE_DEVICES &&
       mm_plan(c->st, mg, c->kcap, nsplit_for(c, c->kcap) * c->kcap).nslot > 0) {
-    size_t free_now = 0, total = 0;
-    if (hipMemGetInfo(&free_now, &total) != hipSuccess) (void)hipGetLastError();
-    const size_t most = std::min(MM_WORKSPACE, free_now / MM_WORKSPACE_SHARE);
-    const size_t want = std::min(slots + (size_t)mg.naux * c->kcap, most / bytes);
+    // (a context as wide as the default is mostly used with narrower blocks, which the least serves)
+    size_t most = slots * bytes <= MM_WORKSPACE_MIN && c->kcap >= 32 ? MM_WORKSPACE_MIN : MM_WORKSPACE;
+    size_t want = std::min(slots + (size_t)mg.naux * c->kcap, most / bytes), free_now = 0, total = 0;
+    if (want * bytes > MM_WORKSPACE_MIN) {
+      if (hipMemGetInfo(&free_now, &total) != hipSuccess) (void)hipGetLastError();
+      want = std::min(want, free_now / MM_WORKSPACE_SHARE / bytes);
+    }
     if (want > slots) {
       const size_t more = (want - slots) * bytes;
       if (g_more[c->device].fetch_add(more) + more <= MM_WORKSPACE_MORE &&

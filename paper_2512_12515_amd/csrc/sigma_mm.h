@@ -25,19 +25,21 @@ constexpr int MM_MIN_TILES_F32 = 18;
 // BF16: fewest column tiles and virtual tiles. us, the one-kernel form -> this one, six / three products:
 // 20/200/700 20 vectors (280 tiles) 4543 -> 4126 / 3060 -> 2737, 10 (140) 2302 -> 2361 / 1586 -> 1438;
 // 20/288/300 20 (360) 4160 -> 3630 / 2658 -> 2150; 40/400/1540 12 (312) 33.2e3 -> 29.9e3 / 20.1e3 -> 16.5e3,
-// 2 (52) 5702 -> 5547 / 3426 -> 3658; 50/500/1800 20 (640) 116e3 -> 82e3 / 65.8e3 -> 46.3e3; 13/117/457 20
+// 2 (52) 5702 -> 5547 / 3426 -> 3658; 50/500/1800 20 (640) 117e3 -> 86e3 / 65.8e3 -> 46.3e3; 13/117/457 20
 // (8 virtual tiles) 814 -> 1092 / 636 -> 722.
 constexpr int BF_MIN_TILES = 160;
 constexpr int BF_MIN_NVT = 13;
 // Fewest aux indices: below, the one-kernel form has a split for every aux index whatever the block
 // width, and a vector's sigma does not depend on the block around it; that stays so.
 constexpr int MM_MIN_NAUX = 96;
-// Workspace that a context outside a slab takes at most, where its least is over MM_WORKSPACE_MIN. FP64 products
-// with the least / 1 GB / 1536 MB / 4 GB, us: 20/200/700, 20 vectors 8435 / 8293 / 7881 / 7740, 10 vectors
-// 4364 / 4251 / 4100 / 3964; 13/117/457, 7 vectors 685 / 546 / 561 / 547. hipMalloc and hipFree of one
-// buffer take 24 us up to 64 MB, 0.3 ms up to 1536 MB, 0.57 ms at 2 GB and 90 to 120 ms from 3 GB on (some
-// hipMallocs after such a hipFree as long), and a build with its release 0.87 ms (13/117/457) and 1.1 ms
-// (20/200/700) up to 1536 MB, 1.2 and 1.4 ms with 4 GB. At 5/20/100 (59 MB) more is no faster.
+// Workspace that a context outside a slab takes at most. FP64 products with the least / 1 GB / 1536 MB / 4 GB, us:
+// 20/200/700, 20 vectors 8435 / 8293 / 7881 / 7740, 10 vectors 4364 / 4251 / 4100 / 3964; 13/117/457, 7 vectors
+// 685 / 546 / 561 / 547. hipMalloc and hipFree of one buffer take 24 us up to 64 MB, 0.3 ms up to 1536 MB,
+// 0.57 ms at 2 GB and 90 to 120 ms from 3 GB on (some hipMallocs after such a hipFree as long), and a
+// build with its release 0.87 ms (13/117/457) and 1.1 ms (20/200/700) up to 1536 MB, 1.2 and 1.4 ms with 4 GB.
+// Contexts of 32 vectors whose least is under MM_WORKSPACE_MIN stay under it: at 5/20/100 (56 MB) 20 vectors
+// take 62 us either way, and the build half of the 0.5 ms. Narrower ones, whose blocks are as wide as the
+// least is made for, do not: 10/60/220, 4 vectors of 4 120 -> 87 us (the one-kernel form 100).
 constexpr size_t MM_WORKSPACE = size_t(1536) << 20;
 constexpr size_t MM_WORKSPACE_MIN = size_t(64) << 20;
 // What all contexts of the process take beyond their least on a device, and the share of the device's free

@@ -118,3 +118,15 @@ def test_nto_weights_with_little_memory():
         torch.cuda.empty_cache()
     for key in ref:
         assert np.max(np.abs(got[key] - ref[key])) <= 1e-12 * np.abs(ref[key]).max(), key
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nocc,nvir,naux,width", [(8, 45, 150, 6), (10, 60, 220, 4), (12, 100, 350, 3), (4, 16, 102, 32)])
+def test_narrow_contexts_have_workspace_for_their_width(nocc, nvir, naux, width, prec):
+    """A context whose largest block is as wide as the product gives the bits of a wider one."""
+    eps, L = gen.orbital_energies(9, nocc, nvir), gen.lpq_full(9, nocc + nvir, naux)
+    out = []
+    for w in (width, 32):
+        with P.PpRPA(eps, L, nocc, prec=prec, max_block=w) as ctx:
+            out.append(ctx.matvec(gen.random_vectors(10, width, ctx.n)))
+    assert np.array_equal(out[0], out[1])
