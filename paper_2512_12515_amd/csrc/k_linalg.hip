@@ -1136,8 +1136,9 @@ __global__ __launch_bounds__(256) void k_triangular_products(const double* __res
       cj[y][tx] = r < m && J * B + tx < m ? T[(size_t)r * m + J * B + tx] : 0.0;
     }
     __syncthreads();
+    const int cn = min(B, m - c0);
 #pragma unroll 8
-    for (int c = 0; c < B; ++c) {
+    for (int c = 0; c < cn; ++c) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         tt[q] += ri[ty + 8 * q][c] * rj[tx][c];
@@ -1677,10 +1678,11 @@ hipError_t launch_svd_vectors(const double* A, int64_t astride, int rows, int co
   return hipGetLastError();
 }
 
-// Eigenvalues of the k Gram matrices G (m x m), descending, on several workgroups each wherever the
-// one-launch reduction takes the order (from 3 on): ten matrices of order 16 / 200 by one workgroup
-// each take 161 us / 2.85 ms, so 70 us / 0.65 ms.
-bool nto_spectra(int m) { return tridiag_fits(m); }
+// Eigenvalues of the k Gram matrices G (m x m), descending, on several workgroups each from order 4 on
+// where the one-launch reduction takes it: ten matrices of order 16 / 200 by one workgroup each take
+// 161 us / 2.85 ms, so 70 us / 0.65 ms (whole calls, ten roots, one workgroup / so, us: order 3 167 / 167, 4
+// 177 / 168, 6 197 / 175, 10 234 / 185, 16 308 / 203).
+bool nto_spectra(int m) { return m >= 4 && tridiag_fits(m); }
 
 size_t nto_work(int k, int nv, int no) {
   return std::max(nto_spectra(nv) ? spectra_work(nv, k) : 0, nto_spectra(no) ? spectra_work(no, k) : 0);

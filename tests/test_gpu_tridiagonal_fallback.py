@@ -56,7 +56,7 @@ def test_dense_solves(nocc, nvir, n):
         assert np.max(np.abs(a - b)) <= tol, i
 
 
-@pytest.mark.parametrize("nocc,nvir,k", [(3, 33, 5), (20, 200, 3), (1, 257, 3)])
+@pytest.mark.parametrize("nocc,nvir,k", [(3, 4, 3), (3, 33, 5), (20, 200, 3), (1, 257, 3)])
 def test_nto_weights(nocc, nvir, k):
     eps, L = gen.orbital_energies(82, nocc, nvir), gen.lpq_full(82, nocc + nvir, 8)
     with P.PpRPA(eps, L, nocc, mult="singlet") as ctx:
