@@ -711,19 +711,28 @@ pprpa_status build_ab_impl(const pprpa_build_ab_args* a, pprpa_ctx* c) {
 
 namespace pprpa {
 
+static hipError_t malloc_or_refuse(pprpa_ctx* c, void** p, size_t bytes) {
+  if (c->refuse > 0) {
+    --c->refuse;
+    *p = nullptr;
+    return hipErrorOutOfMemory;
+  }
+  return hipMalloc(p, bytes);
+}
+
 hipError_t malloc_giving_back(pprpa_ctx* c, void** p, size_t bytes) {
-  hipError_t e = hipMalloc(p, bytes);
+  hipError_t e = malloc_or_refuse(c, p, bytes);
   if (e == hipSuccess || !c->Sp || c->sp_slots == c->sp_least) return e;
   (void)hipGetLastError();
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
   free_more(c);
-  if (hipMalloc(&c->Sp, c->sp_least * c->sp_bytes) != hipSuccess) {  // (the next product tries again)
+  if (malloc_or_refuse(c, &c->Sp, c->sp_least * c->sp_bytes) != hipSuccess) {  // (the next product tries again)
     (void)hipGetLastError();
     c->Sp = nullptr;
   } else {
     c->allocs.push_back(c->Sp);
   }
-  return hipMalloc(p, bytes);
+  return malloc_or_refuse(c, p, bytes);
 }
 
 pprpa_status check_build_args(const pprpa_build_args* a) {
@@ -972,6 +981,14 @@ pprpa_status pprpa_dims(const pprpa_ctx* c, int64_t* n_pp, int64_t* n_hh) {
   if (!c) return einval("ctx is NULL");
   if (n_pp) *n_pp = c->g.nvv;
   if (n_hh) *n_hh = c->g.noo;
+  return PPRPA_OK;
+}
+
+// For the tests (not in the header): the next `count` workspace allocations of the context's calls are
+// refused, as if the device had no memory left.
+pprpa_status pprpa_test_refuse_allocations(pprpa_ctx* c, int32_t count) {
+  if (!c) return einval("ctx is NULL");
+  c->refuse = count;
   return PPRPA_OK;
 }
 

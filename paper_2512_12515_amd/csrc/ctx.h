@@ -28,6 +28,7 @@ struct pprpa_ctx {
   int64_t sp_slots = 0;     // its size in matrices (nmop x nmop of the sigma precision), the least
   int64_t sp_least = 0;     // that every product needs, and the bytes of one
   size_t sp_bytes = 0;
+  int refuse = 0;           // allocations of malloc_giving_back yet to be refused (tests)
   double* zbuf = nullptr;   // [kcap][n] staging of host vectors
   double* sbuf = nullptr;
   double* M = nullptr;      // dense matrix [n][n] (dense builds)
