@@ -309,7 +309,7 @@ pprpa_status pprpa_solve_stats(pprpa_solve* solve, pprpa_kernel_stats* out, int3
  * are admitted in arrival order when their device footprint (staged integrals, sigma buffers,
  * Davidson workspace; computed exactly at submit) fits in the server's HBM arena and one of
  * max_inflight slots is free (more sigma workspace while a quarter of the arena at most is held); every in-flight solve advances independently on its own stream,
- * and the sigma products of all solves that need one at the same time run as one grouped grid.
+ * and the sigma products of all solves that need one at the same time run as grouped grids.
  * A request's arithmetic is the same as pprpa_build + pprpa_davidson with the same arguments
  * (same kernels and decomposition), so its roots do not depend on what it was served with.
  * Threads: an admission thread (builds) and a worker thread (phases, grouped launches); the

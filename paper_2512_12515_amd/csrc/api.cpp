@@ -308,7 +308,8 @@ int staging_chunk(size_t per, int naux) {
   return (int)std::max<size_t>(1, std::min<size_t>((size_t)std::max(naux, 1), cap));
 }
 
-// Whether the stream may use only a part of the device's compute units (a mask without any bit, or none to be had: no).
+// Whether the stream may use only a part of the device's compute units (no: a mask without any bit, or
+// none to be had).
 bool stream_is_masked(hipStream_t s, int device) {
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1) {
@@ -726,7 +727,8 @@ hipError_t malloc_giving_back(pprpa_ctx* c, void** p, size_t bytes) {
   (void)hipGetLastError();
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
   free_more(c);
-  if (malloc_or_refuse(c, &c->Sp, c->sp_least * c->sp_bytes) != hipSuccess) {  // (the next product tries again)
+  // (where even the least is refused, the next product tries again)
+  if (malloc_or_refuse(c, &c->Sp, c->sp_least * c->sp_bytes) != hipSuccess) {
     (void)hipGetLastError();
     c->Sp = nullptr;
   } else {
@@ -1172,7 +1174,8 @@ static pprpa_status nto_ab(pprpa_ctx* c, int k, const double* z, int on_device, 
     if (le == hipSuccess && d_vv) le = hipMemcpyAsync(d_vv, Dv, dv * sizeof(double), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && d_oo && dov)
       le = hipMemcpyAsync(d_oo, Do, dov * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (le == hipSuccess && polls >= 0 && sv) le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && polls >= 0 && sv)
+      le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && polls >= 0 && so)
       le = hipMemcpyAsync(hl + 1, lost + 1, sizeof(int), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess) le = hipStreamSynchronize(s);
@@ -1254,7 +1257,8 @@ pprpa_status pprpa_nto(pprpa_ctx* c, int32_t k, const double* z, int32_t on_devi
     if (le == hipSuccess && d_vv) le = hipMemcpyAsync(d_vv, Dv, mv * sizeof(double), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && d_oo && mo)
       le = hipMemcpyAsync(d_oo, Do, mo * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (le == hipSuccess && polls >= 0 && sv) le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
+    if (le == hipSuccess && polls >= 0 && sv)
+      le = hipMemcpyAsync(hl, lost, sizeof(int), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess && polls >= 0 && so)
       le = hipMemcpyAsync(hl + 1, lost + 1, sizeof(int), hipMemcpyDeviceToHost, s);
     if (le == hipSuccess) le = hipStreamSynchronize(s);

@@ -629,8 +629,8 @@ static hipError_t launch_sigma_group_fused(const GroupMember* m, int n, hipStrea
 // Members of the two-product form in BF16 each fill the chip (160 column tiles and more): one after the
 // other. In FP64 and FP32 a product of a few virtual tiles does not, and a served one takes several launches,
 // each with a tail: theirs go side by side (ms of sigma of the same served products one after the other /
-// side by side / in the one-kernel form: 5/20/100 FP64, 10 vectors 15.2 / 9.8 / 12.0; 13/117/457 FP64, 4 vectors
-// 176 / 136 / 145; 20/200/700 FP64, 5 vectors 401 / 376 / 450).
+// side by side / in the one-kernel form: 5/20/100 FP64, 10 vectors 15.2 / 9.8 / 12.0; 13/117/457 FP64, 4
+// vectors 176 / 136 / 145; 20/200/700 FP64, 5 vectors 401 / 376 / 450).
 // The rest as one grid (two in FP64, which has two kernels for the rest).
 hipError_t launch_sigma_group(const GroupMember* m, int n, hipStream_t s) {
   if (n <= 0) return hipSuccess;

@@ -29,9 +29,8 @@
 // What bounds it: the loads' latency with one stage (six products) in flight, and T's conversion and
 // store in phase 1: with the products cut to a sixth 83 ms of 101 remained, with no loads 69; the
 // matrix pipe is busy 60 % of phase 2. Times (us), one-kernel form before -> now: 50/500/1800 six
-// products 116573 -> 84834 (20 vectors; 1.06 PFLOP/s of BF16
-// products, 3/4 of the full contraction's), 40/400/1540 three
-// 26903 -> 21472.
+// products 116573 -> 84000 to 88900 by card (20 vectors; 1.01 to 1.07 PFLOP/s of BF16 products, 3/4 of the
+// full contraction's), 40/400/1540 three 26903 -> 20900 to 22300.
 #include "internal.h"
 #include "sigma_bf16.h"
 #include "sigma_mm.h"

@@ -30,13 +30,16 @@
 //     runs phase 2 of part c - 1 of every slot and phase 1 of part c, whose short units fill the
 //     long ones' tail. Where the workspace is small (served requests) a launch takes some slots whole
 //     instead, if enough products are in it to fill the chip: the sums then stay in registers (a part of
-//     one aux index reads and writes them every 9 stages at 13/117/457). FP32 sums are chains of one aux index (16 times the c tiles), added up in
-//     FP64 in registers: 7.8e-8 relative error at 40/400/1540, against 2.3e-7 of the one-kernel form.
+//     one aux index reads and writes them every 9 stages at 13/117/457). FP32 sums are chains of one
+//     aux index (16 times the c tiles), added up in FP64 in registers: 7.8e-8 relative error at
+//     40/400/1540, against 2.3e-7 of the one-kernel form.
 // What bounds it: the matrix pipe, busy 87 % of the time at 50/500/1800 (61 % before); the direct
 // loads cost 6.7 %, the barriers 1.6 %, launch tails about 2 %. Times (us; 12-20 vectors):
-//   FP64 50/500/1800 354518 -> 242396 (60 TFLOP/s of the 3/4 of the products the identity needs;
-//   a large library product reaches 73), 20/200/700 10381 -> 7662, 13/117/457 (7 vectors) 716 -> 506;
-//   FP32 40/400/1540 45015 -> 35584; alpha-beta 200/20/18 FP64 7605 -> 5661, FP32 4389 -> 3059.
+//   FP64 50/500/1800 354518 -> 243000 (60 TFLOP/s of the 3/4 of the products the identity needs;
+//   a large library product reaches 73), 20/200/700 10381 -> 7850, 13/117/457 (7 vectors) 716 -> 504;
+//   FP32 40/400/1540 45015 -> 35900; alpha-beta 200/20/18 FP64 7605 -> 5870, FP32 4389 -> 3059.
+//   FP64 sums are one chain a slot: the error against 64-bit references is 2.0e-15 at 50/500/1800, 9.0e-16
+//   with the one-kernel form's many short sums (20/200/700 8.9e-16 and 7.3e-16).
 #include "internal.h"
 #include "sigma_common.h"
 #include "sigma_mm.h"
@@ -599,8 +602,8 @@ static int mm_whole_slots(const MmGeometry& g, const MmProduct& a) {
   return (int)(mm_room(a) / 2 / ((int64_t)len * a.k));
 }
 
-// Kernel arguments of a product, but for those of one launch (step). slots: those of a launch, whole, or 0: all, in
-// parts.
+// Kernel arguments of a product, but for those of one launch (step). slots: those of a launch, whole, or
+// 0: all, in parts.
 static hipError_t mm_params(Store st, const MmGeometry& g, const MmProduct& a, int slots, MmParams& p) {
   const MmPlan& m = a.m;
   const int k = a.k;
@@ -684,9 +687,9 @@ hipError_t launch_sigma_mm_group(Store st, const MmGeometry* g, const MmProduct*
     if (mm_room(a[i]) < std::min(2, mm_len(g[i], a[i])) * (int64_t)a[i].k * a[i].m.nslot)
       return hipErrorInvalidValue;
   // runs of whole slots where they make enough phase 2 units a launch (with the phase 1 units beside them,
-  // about as much work). Sigma time of 448 served products at 13/117/457 in FP32, 8 vectors, ms, for at least 256 /
-  // 96 / 32 units: 151 / 132 / 133; 512 with 4 vectors, 32 solves in flight 110 / 106 / 108, 4 in flight
-  // 113 / 117 / 133.
+  // about as much work). Sigma time of 448 served products at 13/117/457 in FP32, 8 vectors, ms, for at
+  // least 256 / 96 / 32 units: 151 / 132 / 133; 512 with 4 vectors, 32 solves in flight 110 / 106 / 108, 4 in
+  // flight 113 / 117 / 133.
   int64_t units = 0;
   for (int i = 0; i < n; ++i) units += (int64_t)a[i].m.items2v * mm_whole_slots(g[i], a[i]);
   MmParams p[GROUP_MAX];

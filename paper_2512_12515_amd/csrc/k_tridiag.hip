@@ -24,9 +24,9 @@
 // piece (1.3 us from store to all workgroups having read, 2 with p in row order), and a reader
 // polls until it differs.
 //
-// What bounds it: latency, 2.4 us a step at n = 225 and 3.9 at n = 1071 (the exchange 1.3 and 1.9,
+// What bounds it: latency, 2.4 us a step at n = 225 and 3.8 at n = 1071 (the exchange 1.3 and 1.9,
 // the rest three sums over a wave, three barriers, a square root and a reciprocal, one after the
-// other); as two launches a step 6.4 and 11.2. In all 0.54 ms and 4.12 ms, before 1.44 and 11.96;
+// other); as two launches a step 6.4 and 11.2. In all 0.54 ms and 4.07 ms, before 1.44 and 11.96;
 // 6.2 us a step at n = 1989, the widest rows, before 16.8.
 //
 // Every wait ends: a workgroup's stores of step k depend on its own earlier steps and on the other

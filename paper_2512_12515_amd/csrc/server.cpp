@@ -5,8 +5,8 @@
 //   workspace) inside the server's HBM arena, and a free slot (stream + pinned status buffer).
 //   A request that does not fit waits until finished requests release memory; one larger than
 //   the whole arena fails with ENOMEM. As long as three quarters of the arena stay free, a request
-//   gets what more workspace its sigma products can use (fewer, longer parts). The build and the initial subspace run on the slot's
-//   stream; after that the caller's input buffers are no longer read.
+//   gets what more workspace its sigma products can use (fewer, longer parts). The build and the
+//   initial subspace run on the slot's stream; after that the caller's input buffers are no longer read.
 // * Progress (worker thread): every in-flight solve is a Davidson phase machine. Each pass the
 //   worker advances every solve whose stream has drained. A solve that needs a sigma product has
 //   its block unpacked at once on its own stream; the solves waiting for sigma are then launched

@@ -32,9 +32,9 @@ constexpr int BF_MIN_NVT = 13;
 // Fewest aux indices: below, the one-kernel form has a split for every aux index whatever the block
 // width, and a vector's sigma does not depend on the block around it; that stays so.
 constexpr int MM_MIN_NAUX = 96;
-// Workspace that a context outside a slab takes at most. FP64 products with the least / 1 GB / 1536 MB / 4 GB, us:
-// 20/200/700, 20 vectors 8435 / 8293 / 7881 / 7740, 10 vectors 4364 / 4251 / 4100 / 3964; 13/117/457, 7 vectors
-// 685 / 546 / 561 / 547. hipMalloc and hipFree of one buffer take 24 us up to 64 MB, 0.3 ms up to 1536 MB,
+// Workspace that a context outside a slab takes at most. FP64 products with the least / 1 GB / 1536 MB /
+// 4 GB, us: 20/200/700, 20 vectors 8435 / 8293 / 7881 / 7740, 10 vectors 4364 / 4251 / 4100 / 3964;
+// 13/117/457, 7 vectors 685 / 546 / 561 / 547. hipMalloc and hipFree of one buffer take 24 us up to 64 MB, 0.3 ms up to 1536 MB,
 // 0.57 ms at 2 GB and 90 to 120 ms from 3 GB on (some hipMallocs after such a hipFree as long), and a
 // build with its release 0.87 ms (13/117/457) and 1.1 ms (20/200/700) up to 1536 MB, 1.2 and 1.4 ms with 4 GB.
 // Contexts of 32 vectors whose least is under MM_WORKSPACE_MIN stay under it: at 5/20/100 (56 MB) 20 vectors
@@ -101,8 +101,8 @@ struct MmParams {
   int64_t ustride, lbstride, qstride, qostride;
 };
 
-// Workspace beyond `slots` matrices that a product of k vectors uses to advantage, in matrices: that of parts of
-// MM_PART aux indices. A served request gets it while the arena is mostly free (requests/s, least -> more
+// Workspace beyond `slots` matrices that a product of k vectors uses to advantage, in matrices: that of
+// parts of MM_PART aux indices. A served request gets it while the arena is mostly free (requests/s, least -> more
 // workspace, the one-kernel form in brackets; 13/117/457, 4 roots, 32 solves in flight: FP64 322 -> 345 (311),
 // FP32 389 -> 457 (403); 4 in flight: 239 -> 277 (254), 289 -> 347 (318)).
 constexpr int MM_PART = 8;
